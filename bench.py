@@ -652,7 +652,7 @@ def class_work(shape, R, B):
 
 
 KERNEL_SOURCES = {  # sources whose text fixes a kernel class's code
-    "attn_self": ["rc_attn3.hip", "rc_common.h", "rc_internal.h", "rc_launch.h"],
+    "attn_self": ["rc_attn4.hip", "rc_common.h", "rc_internal.h", "rc_launch.h"],
     "attn_cross": ["rc_attn2.hip", "rc_common.h", "rc_internal.h", "rc_launch.h"],
     "gemm": ["rc_gemm2.hip", "rc_common.h", "rc_internal.h", "rc_launch.h"],
 }

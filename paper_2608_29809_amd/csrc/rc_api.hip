@@ -441,21 +441,15 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
     RC_TRY(timed(c, RC_KC_EMBED, s, [&] { return rc::launch_embed<T>(ea, R, s); }));
   }
 
-  // self-attention key splits: fill 2 workgroups x 256 CUs with as few
-  // splits as possible (the bf16 kernel takes uneven splits)
-  long qtiles = 0;
-  for (int b = 0; b < B; ++b) qtiles += (counts[b] + 127) / 128;
-  int splits = 1;
+  // self-attention: query halves per wave and key splits
+  int splits = 1, attn_qh = 1;
   if (sizeof(T) == 2) {
-    double best = -1.0;
-    const int max_s = std::min(N / 64, 16);
-    for (int sp = 1; sp <= max_s; ++sp) {
-      if ((long)R * sp > part_cap_rows(R) && sp > 1) break;
-      const long wgs = qtiles * H * sp;
-      const double eff = wgs / (std::ceil(wgs / 512.0) * 512.0) - 0.01 * sp;  // 2 workgroups per CU
-      if (eff > best) { best = eff; splits = sp; }
-    }
+    const rc::AttnPlan pl = rc::plan_attention(counts.data(), B, H, N, part_cap_rows(R));
+    splits = pl.splits;
+    attn_qh = pl.qh;
   } else {
+    long qtiles = 0;
+    for (int b = 0; b < B; ++b) qtiles += (counts[b] + 127) / 128;
     while (splits < kMaxSplits && qtiles * H * splits < 512 && N % (64 * splits * 2) == 0 &&
            (long)R * splits * 2 <= part_cap_rows(R))
       splits *= 2;
@@ -514,6 +508,7 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
       g.A = A1; g.W = lw.qkv_w; g.bias = lw.qkv_b; g.M = R; g.N = 3 * C; g.K = C; g.lda = C;
       g.out = Q; g.ldo = C; g.rows = rows; g.kslot = Ks; g.vslot = Vs;
       g.chain_stride = slot_chain_stride; g.tokens = N; g.hidden = C;
+      g.q_scale = scale_log2;  // (bf16: the self-attention exponentiates the scores as they are)
       g.warm = lw.proj_w; g.warm_lines = wlines(C, C);
       RC_TRY(gemm<T>(c, RC_KC_GEMM_QKV, g, rc::EPI_QKV, gpart, gpf, s));
     }
@@ -524,7 +519,7 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
       a.O = O; a.Opart = part; a.ML = ml; a.total_rows = R; a.scale_log2 = scale_log2;
       if (dense) { a.warm = lw.xq_w; a.warm_lines = wlines(C, C); }
       RC_TRY(timed(c, RC_KC_ATTN_SELF, s, [&] {
-        return sizeof(T) == 2 ? rc::launch_attention3(a, B, max_rb, s)
+        return sizeof(T) == 2 ? rc::launch_attention4(a, B, max_rb, attn_qh, s)
                               : rc::launch_attention<T>(a, B, max_rb, false, s);
       }));
       if (splits > 1)

@@ -3,7 +3,7 @@
 // the localisation maps (Sec. 3.2).  The text values are stored transposed
 // ([72][keys] per head).
 //
-// Operand layouts shared with the self-attention (rc_attn3.hip): scores are
+// Operand layouts shared with the self-attention (rc_attn4.hip): scores are
 // formed transposed (S^T = K Q^T) so each lane owns one query, and the
 // probabilities are reused in registers as the B operand of O^T = V^T P^T.
 // * Key order inside a 32-key sub-tile: the K row that lane m supplies is

@@ -136,6 +136,15 @@ __device__ __forceinline__ void lds_dma16(const void *gsrc, const void *lds_wave
                : "memory", "m0");
 }
 
+// The same copy with a wave-uniform base address and a 32-bit byte offset per
+// lane: one address register per lane however many bases are in use.
+__device__ __forceinline__ void lds_dma16s(const void *base, unsigned lane_off, const void *lds_wave_base) {
+  const unsigned dst = __builtin_amdgcn_readfirstlane(
+      (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char *)lds_wave_base);
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(lane_off), "s"(dst), "s"(base)
+               : "memory", "m0");
+}
+
 // Memory-side cache warm-up of a buffer a later kernel reads: one dword of
 // each 128-byte line is copied into a 256-byte LDS scratch of the calling
 // wave that nothing reads, so no register is held; the lines are then

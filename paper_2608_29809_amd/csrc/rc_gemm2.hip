@@ -65,7 +65,7 @@ __device__ __forceinline__ void epi_store(const GemmArgs &g, int m, int n, float
     }
   } else if (EPI == EPI_QKV) {
     if (part == 0) {
-      ((bf16 *)g.out)[(size_t)m * g.ldo + n] = (bf16)v;
+      ((bf16 *)g.out)[(size_t)m * g.ldo + n] = (bf16)(v * g.q_scale);
     } else {
       const int pk = g.rows[m];
       const size_t cb = (size_t)row_chain(pk) * g.chain_stride;
@@ -496,6 +496,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm2_kernel(GemmArgs g, 
         } else {
 #pragma unroll
           for (int q = 0; q < 4; ++q) v[q] = tile_at(row, c4 + q) + bb[q];
+          if (EPI == EPI_QKV && tile_part == 0)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] *= g.q_scale;
         }
         if (EPI == EPI_RESID) {
           f32x4 x;

@@ -40,6 +40,7 @@ struct GemmArgs {
   long long chain_stride;  // elements between consecutive chains' slots
   int tokens;              // N tokens per chain
   int hidden;              // C
+  float q_scale;           // EPI_QKV: factor of the stored queries
   // EPI_TEXTKV
   void *tkv;        // entry (layer, chain 0)
   int text_len, text_pad;
@@ -85,7 +86,7 @@ struct AttnArgs {
   int hidden;            // C = heads*72
   int splits;            // key-range splits (grid.y = heads*splits)
   void *O;               // [R][C] E output (splits == 1)
-  float *Opart;          // [splits][R][C] split outputs (splits > 1): fp32 unnormalised (fp32 path) or bf16 normalised (launch_attention3)
+  float *Opart;          // [splits][R][C] split outputs (splits > 1): fp32 unnormalised (fp32 path) or bf16 normalised (launch_attention4)
   float *ML;             // [splits][R][heads][2] running max (log2 domain) and sum
   int total_rows;        // R (stride of the partial arrays)
   // map emission (cross-attention)
@@ -149,10 +150,13 @@ template <typename T> hipError_t launch_attention(const AttnArgs &a, int n_chain
 // a.pmaps is set (rc_attn2.hip).  hidden 1152, at most 128 keys, one key
 // range.
 hipError_t launch_attention2q(const AttnArgs &a, int n_chains, int max_rows, hipStream_t s);
-// bf16 self-attention with the next tile's score MFMAs overlapping the
-// softmax (rc_attn3.hip); no map emission.
-hipError_t launch_attention3(const AttnArgs &a, int n_chains, int max_rows, hipStream_t s);
-// Split combine for launch_attention3: Opart holds normalised bf16 split
+// bf16 self-attention (rc_attn4.hip); queries multiplied by log2(e)/sqrt(72).
+// The plan holds the 32-query halves per wave and the key splits, of at most
+// max_split_rows rows x splits in all.
+struct AttnPlan { int qh, splits; };
+AttnPlan plan_attention(const int *counts, int n_chains, int heads, int n_keys, long max_split_rows);
+hipError_t launch_attention4(const AttnArgs &a, int n_chains, int max_rows, int qh, hipStream_t s);
+// Split combine for launch_attention4: Opart holds normalised bf16 split
 // outputs [splits][R][C], ML the log2-domain maxima and denominators.
 hipError_t launch_attn_combine_norm(const void *Opart, const float *ML, void *O, int R, int heads, int splits,
                                     hipStream_t s);

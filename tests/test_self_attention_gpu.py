@@ -1,0 +1,77 @@
+"""Self-attention of one block at the edges of its tiles, splits and softmax
+range, through the block call, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import synth
+from _cases import download_slot, relerr, upload_slot
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_2608_29809_amd.runtime import ActiveSet, RegionCacheModel
+
+
+def _block(gh, gw, counts, seed, edit=None):
+    """A bf16 reuse block of len(counts) chains over gh x gw tokens; returns
+    (per chain) the errors of H and of the attention's own change of H."""
+    s = synth.ModelShape(layers=1, text_dim=1152, grid_h=gh, grid_w=gw, dtype="bf16", token_mode=True)
+    W = synth.make_weights(s, seed=seed, stress=True)
+    if edit:
+        edit(W["layers"][0])
+    B, N, C = len(counts), s.tokens, s.hidden
+    rng = np.random.default_rng(seed)
+    idx = [np.sort(rng.choice(N, size=n, replace=False)).astype(np.int32) for n in counts]
+    slot = synth.make_cache_slot(s, B, seed)
+    if edit:  # cached keys like the block's own
+        slot["K"] = synth.bf16_round(slot["K"] * 0.1 + W["layers"][0]["qkv_b"][C:2 * C].reshape(1, 1, 16, 1, 72))
+    x = synth.bf16_round(rng.standard_normal((B, N, C)).astype(np.float32))
+    t_vec = rng.standard_normal(C).astype(np.float32)
+    text = synth.make_text(s, B, seed)
+    model = RegionCacheModel(s, W)
+    cache = model.alloc_cache(B, 1)
+    upload_slot(model, cache, 0, slot)
+    tkv = model.prepare_text(model.to_storage(text))
+    model.reuse_step(cache, 0, ActiveSet.from_lists(idx), model.to_storage(x), 0, -1, tkv,
+                     t_vec=torch.from_numpy(t_vec).cuda())
+    torch.cuda.synchronize()
+    got = download_slot(cache, 0, 1, B)
+    for b in range(B):
+        if not counts[b]:
+            continue
+        X, K, V, H, _ = O.reuse_block_tokens(s, W, x[b], idx[b], t_vec, text[b], slot["K"][0, b], slot["V"][0, b],
+                                             slot["H"][0, b])
+        # bf16 operands and storage (the tolerance of the block tests)
+        assert relerr(got["H"][0, b][idx[b]], np.asarray(H)[idx[b]]) < 2e-2, (b, counts[b])
+        assert relerr(got["K"][0, b], K) < 2e-2 and relerr(got["V"][0, b], V) < 2e-2, (b, counts[b])
+
+
+@pytest.mark.parametrize("gh,gw,counts", [(8, 8, [1]), (8, 8, [64]), (8, 16, [33, 0, 128]), (8, 24, [32, 31, 65]),
+                                          (16, 20, [129, 127]), (32, 32, [257, 255, 256])])
+def test_edges(gh, gw, counts):
+    """One to sixteen key tiles, query counts around the 32-query halves and
+    the 128-query tiles, an empty chain."""
+    print("self-attention", gh, gw, counts, flush=True)
+    _block(gh, gw, counts, seed=gh + gw)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_softmax_range(sign):
+    """All logits of every query near +-136 (+-196 in base 2), outside the range
+    of the fixed reference: the workgroups start again relative to their
+    maxima.  Queries and keys are 4 and +-4 plus a tenth of their usual
+    variation; rounding them to bf16 (half a unit of 2^-6) moves a logit by
+    about 4 * 0.0045 * sqrt(2 * 72) / sqrt(72) = 0.025, and the attention by a
+    few per cent of a mean of hundreds of values, well under 2e-2 of H."""
+
+    def edit(lw):
+        C = 1152
+        lw["qkv_w"][:2 * C] *= 0.1
+        lw["qkv_w"][:] = synth.bf16_round(lw["qkv_w"])
+        lw["qkv_b"][:C] = 4.0
+        lw["qkv_b"][C:2 * C] = 4.0 * sign
+
+    print("softmax range", sign, flush=True)
+    _block(16, 16, [200, 3], seed=5, edit=edit)
