@@ -116,7 +116,7 @@ constexpr int kMaxSplits = 8;
 int part_cap_rows(int max_rows) { return kMaxSplits * std::min(max_rows, 1024); }
 
 struct WsLayout {
-  size_t rows, offsets, X, A1, Q, O, G, part, ml, pmaps, e, th, temb, t0, gpart, fstats, fextra, total;
+  size_t rows, offsets, X, A1, Q, O, G, part, ml, pmaps, e, th, temb, t0, gpart, fstats, fextra, fuv, total;
   size_t gpart_floats;
   size_t txt_h, txt_y, txt_total;
 };
@@ -145,6 +145,7 @@ WsLayout ws_layout(const rc_ctx *c, int max_rows, int B) {
   w.gpart = take(w.gpart_floats * 4);
   w.fstats = take(R * rc::kFoldMaxTiles * 8 + 256);  // + the 16-byte reads' overhang
   w.fextra = take((size_t)4 * c->C * c->esz);
+  w.fuv = take(c->esz == 2 ? (size_t)c->L * 2 * c->F * 4 : 0);
   w.total = o;
   // text preparation reuses the front of the workspace
   size_t t = 0;
@@ -266,8 +267,10 @@ rc_status gemm(rc_ctx *c, int cls, const rc::GemmArgs &g, int epi, float *part, 
                const rc::LnNext *ln = nullptr, bool *ln_done = nullptr) {
   if (ln_done) *ln_done = false;
   if constexpr (sizeof(T) == 2) {
-    const rc::GemmPlan pl = rc::plan_gemm2(g.M, g.N, g.K, part ? part_floats : 0);
-    RC_TRY(timed(c, cls, s, [&] { return rc::launch_gemm2(g, epi, pl, part, s); }));
+    const rc::GemmPlan pl = rc::plan_gemm(g.M, g.N, g.K, part ? part_floats : 0, epi);
+    RC_TRY(timed(c, cls, s, [&] {
+      return pl.big ? rc::launch_gemm3(g, epi, pl, part, s) : rc::launch_gemm2(g, epi, pl, part, s);
+    }));
     if (pl.splits == 1) return RC_OK;
     return timed(c, RC_KC_SPLIT_FINISH, s, [&] { return rc::launch_gemm2_finish(g, epi, pl, part, s, ln, ln_done); });
   } else {
@@ -389,6 +392,7 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
   const size_t gpf = wl.gpart_floats;
   float2 *fstats = (float2 *)(wsb + wl.fstats);
   void *fextra = wsb + wl.fextra;
+  float *fuv = (float *)(wsb + wl.fuv);
   // bf16: the MLP-up LayerNorm folds into the GEMMs on either side of it
   // when both run unsplit.  The cross out-projection's epilogue writes each
   // row's mean and sum of squared deviations over its column tile and the
@@ -397,9 +401,12 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
   // h W^T = r (x~ W^T - mean u) + v after its K loop (u, v: the products of
   // those rows).
   int fold_nt = 0;
+  bool fold_uv = false;
   if (sizeof(T) == 2) {
-    const rc::GemmPlan px = rc::plan_gemm2(R, C, C, gpf), p1 = rc::plan_gemm2(R, F, C, gpf);
-    if (px.splits == 1 && p1.splits == 1 && C % px.bn == 0 && C / px.bn <= rc::kFoldMaxTiles) fold_nt = C / px.bn;
+    const rc::GemmPlan px = rc::plan_gemm(R, C, C, gpf, rc::EPI_RESID), p1 = rc::plan_gemm(R, F, C, gpf, rc::EPI_GELU);
+    const int tile = px.big ? 144 : px.bn;  // producer's statistics tiles
+    if (px.splits == 1 && p1.splits == 1 && C % tile == 0 && C / tile <= rc::kFoldMaxTiles) fold_nt = C / tile;
+    fold_uv = fold_nt && p1.big;
   }
 
   if (dense) RC_TRY(timed(c, RC_KC_MISC, s, [&] { return rc::launch_dense_offsets((int *)offsets_dev, B, N, s); }));
@@ -421,6 +428,18 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
       return rc::launch_gemv<T>(W.tblock_w, W.tblock_b, temb, 6 * C, C, 1, 0, t0, s);
     }));
   }
+
+  if (fold_uv)
+    for (int l0 = 0; l0 < L; l0 += rc::FoldUvArgs::kLayers) {
+      rc::FoldUvArgs fa{};
+      const int nl = std::min(L - l0, rc::FoldUvArgs::kLayers);
+      for (int l = 0; l < nl; ++l) {
+        fa.w[l] = c->layers[l0 + l].fc1_w;
+        fa.sst[l] = c->layers[l0 + l].sst;
+      }
+      fa.t0 = t0; fa.uv = fuv; fa.l0 = l0; fa.C = C; fa.F = F; fa.shift_row = 3;
+      RC_TRY(timed(c, RC_KC_COND, s, [&] { return rc::launch_fold_uv(fa, nl, s); }));
+    }
 
   // entry: gather + embed the computed tokens
   {
@@ -586,6 +605,7 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
       g.A = A1; g.W = lw.fc1_w; g.bias = lw.fc1_b; g.M = R; g.N = F; g.K = C; g.lda = C; g.out = G; g.ldo = F;
       if (dense && l + 1 < L) { g.warm = c->layers[l + 1].qkv_w; g.warm_lines = wlines(3 * C, C); }
       if (fold_nt) { g.fold_stats = fstats; g.fold_nt = fold_nt; g.fold_extra = fextra; g.fold_eps = c->cfg.ln_eps; }
+      g.fold_u = fuv + (size_t)2 * l * F; g.fold_v = g.fold_u + F;
       RC_TRY(gemm<T>(c, RC_KC_GEMM_FC1, g, fold_nt ? rc::EPI_GELU_FOLD : rc::EPI_GELU, gpart, gpf, s));
     }
     {  // MLP down + gate + residual; merge into the cached hidden state

@@ -96,7 +96,8 @@ __device__ __forceinline__ float wave_max(float v) {
 // exp2 and one reciprocal.  Saturates to x / 0 correctly for large |x|.
 __device__ __forceinline__ float gelu_tanh(float x) {
   constexpr float k = -2.0f * 0.7978845608028654f * 1.4426950408889634f;  // -2 sqrt(2/pi) log2(e)
-  const float e = exp2f(k * x * (1.0f + 0.044715f * x * x));
+  // (the raw instruction: where it flushes a result below 2^-126, 1 + e is 1 either way)
+  const float e = __builtin_amdgcn_exp2f(k * x * (1.0f + 0.044715f * x * x));
   return x * __builtin_amdgcn_rcpf(1.0f + e);
 }
 __device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
@@ -141,7 +142,10 @@ __device__ __forceinline__ void lds_dma16(const void *gsrc, const void *lds_wave
 __device__ __forceinline__ void lds_dma16s(const void *base, unsigned lane_off, const void *lds_wave_base) {
   const unsigned dst = __builtin_amdgcn_readfirstlane(
       (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char *)lds_wave_base);
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(lane_off), "s"(dst), "s"(base)
+  const uint64_t u = (uint64_t)(uintptr_t)base;  // (the scalar operand, also where the compiler kept it in vectors)
+  const uint64_t src = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32 |
+                       (unsigned)__builtin_amdgcn_readfirstlane((int)u);
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(lane_off), "s"(dst), "s"(src)
                : "memory", "m0");
 }
 

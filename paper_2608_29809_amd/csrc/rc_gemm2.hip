@@ -23,6 +23,7 @@
 #include "rc_launch.h"
 #include "rc_internal.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace rc {
@@ -716,8 +717,8 @@ static void launch_reduce(const GemmArgs &a, int epi, int splits, const float *p
 // 4x2-wave 128x128 QKV tiles (16.3 against 16.8 us), nothing for the
 // 2x4-wave MLP-up tiles.  Two K groups of 2x2 waves beat one group of 2x4
 // for 64x128 tiles at ~400 rows (13.3 against 13.6 us).
-GemmPlan plan_gemm2(int M, int N, int K, size_t partial_cap_floats) {
-  GemmPlan p{64, 128, 1, 1, 2, 2, 2};
+static GemmPlan plan_small(int M, int N, int K, size_t partial_cap_floats) {
+  GemmPlan p{64, 128, 1, 1, 2, 2, 2, false};
   const int nk = K / G2_BK;
   const long tn = N / 128;
   const long t32 = (long)((M + 31) / 32) * tn, t64 = (long)((M + 63) / 64) * tn, t128 = (long)((M + 127) / 128) * tn;
@@ -761,6 +762,57 @@ GemmPlan plan_gemm2(int M, int N, int K, size_t partial_cap_floats) {
   } else if (nk % 2 == 0 && t32 <= 256) set(32, 2, 3, 1, 4);
   else if (nk % 2 == 0 && t64 <= 256) set(64, 2, 3, 2, 2);
   else if (t64 <= 512) set(64, 1, 3, 2, 4);
+  return p;
+}
+
+// Large tiles (launch_gemm3) where their estimated time is less.  Estimates in
+// us, fitted to launches of the step's shapes at 723 to 16384 rows (N 1152,
+// 3456, 4608; K 1152, 4608):
+// * this file's kernels: wide outputs 25 per round of 512 128x128 tiles (17
+//   where one round of 256 holds them); narrow ones 9 + 0.031 per 64x128 tile,
+//   at K = 4608 16 + 0.1 per tile and, split in two, 8 + 0.13 with the sum
+//   (11 more where two halves of 64x128 tiles of two K groups, one workgroup
+//   per CU, take a second round);
+// * large tiles: per round, the stages' time and the ends (first stage,
+//   epilogue); a residual epilogue's ends are at least its traffic at 5.5 TB/s;
+//   with two workgroups per CU the ends overlap the other's stages but for 6;
+// * a split sum is its bytes and its launch, and an unsplit MLP-down pays for
+//   the LayerNorm pass that a split sum would include.
+// Measured, this file's kernels against the choice: MLP-up 68 -> 54 us at 4096
+// rows and 232 -> 203 at 16384, 27 -> 20 at 1024; QKV 49.5 -> 42.5 and
+// 175 -> 142, 40 -> 28.5 at 2458; MLP-down 74 -> 50 at 4096 and 247 -> 170;
+// out-projections 27 -> 22.5 and 82 -> 70.
+GemmPlan plan_gemm(int M, int N, int K, size_t partial_cap_floats, int epi) {
+  const GemmPlan small = plan_small(M, N, K, partial_cap_floats);
+  if (epi == EPI_TEXTKV || N % 144 || K % 64 || M < 256) return small;
+  const bool down = K >= 2048 && epi == EPI_RESID;
+  const double t64 = std::ceil(M / 64.0) * (N / 128.0), t128 = std::ceil(M / 128.0) * (N / 128.0);
+  const double mn = (double)M * N, norm = down ? 2.0 + mn * 6.0 / 4e6 : 0.0;
+  double best = N >= 3072 ? (t128 <= 256 ? 17.0 : 25.0 * std::ceil(t128 / 512))
+                : K < 2048 ? 9.0 + 0.031 * t64
+                : small.splits > 1 ? 8.0 + 0.13 * t64 + (t64 > 128 && t64 < 160 ? 11.0 : 0.0) : 16.0 + 0.1 * t64 + norm;
+  GemmPlan p = small;
+  struct Tile { int bm, bn, kg, slots; double stage, ends[3]; };  // ends: stores, residual, GELU
+  static const Tile tiles[] = {{256, 288, 1, 256, 0.90, {12.0, 17.0, 20.0}},
+                               {256, 144, 2, 256, 0.95, {9.0, 13.0, 11.5}},
+                               {128, 144, 2, 256, 0.50, {6.0, 8.0, 8.0}},
+                               {128, 288, 1, 512, 1.10, {10.0, 14.0, 10.0}}};
+  const int kind = epi == EPI_RESID ? 1 : epi == EPI_GELU || epi == EPI_GELU_FOLD ? 2 : 0;
+  for (const Tile &t : tiles)
+    for (int sp = 1; sp <= 4; sp *= 2) {
+      if (N % t.bn || K % (32 * t.kg * sp) || (epi == EPI_QKV && (N / 3) % t.bn)) continue;
+      if (sp > 1 && (!down || (size_t)sp * M * N > partial_cap_floats)) continue;
+      const double wgs = std::ceil((double)M / t.bm) * (N / t.bn) * sp, nst = (double)K / (32 * t.kg * sp);
+      const double rounds = std::ceil(wgs / t.slots);
+      double ends = rounds * t.ends[kind];
+      if (kind == 1 && sp == 1) ends = std::max(ends, mn * 10.0 / 5.5e6);
+      double us = (t.slots > 256 ? 9.0 : 3.0) + rounds * nst * t.stage + ends;
+      us += sp > 1 ? 4.0 + mn * 4.0 * (sp + 2) / 4e6 : norm;
+      if (us < best) {
+        best = us;
+        p = GemmPlan{t.bm, t.bn, sp, t.kg, 0, 0, 0, true};
+      }
+    }
   return p;
 }
 

@@ -64,6 +64,7 @@ struct GemmArgs {
   float2 *fold_stats;          // [M][fold_nt] (mean, sum of squared deviations)
   int fold_nt;                 // producer column tiles (K / fold_nt columns each)
   void *fold_extra;            // [4][C] E
+  const float *fold_u, *fold_v; // [N] u and v (consumer of launch_gemm3, in place of fold_extra)
   float fold_eps;              // consumer
 };
 // most producer column tiles a folded LayerNorm merges per row
@@ -122,8 +123,11 @@ struct GemmPlan {
   int bm, bn, splits, kg;  // kg: K groups inside one workgroup
   int stages;              // LDS ring depth per K group
   int wgm, wgn;            // waves of one K group along M and N (4 or 8 waves)
+  bool big;                // launch_gemm3's tiles (bm, bn, kg, splits)
 };
-GemmPlan plan_gemm2(int M, int N, int K, size_t partial_cap_floats);
+// Tiles, split and kernel of a bf16 GEMM with epilogue `epi`; the folded
+// MLP-up epilogue plans as EPI_GELU.
+GemmPlan plan_gemm(int M, int N, int K, size_t partial_cap_floats, int epi);
 // LayerNorm + modulation of the next block applied to the rows a residual
 // GEMM has just completed: out = E(LN(X) * (1 + scale) + shift) with shift and
 // scale = rows shift_row and shift_row+1 of sst + t0.
@@ -137,6 +141,20 @@ struct LnNext {
 // The tiles of a bf16 GEMM; with a split plan they write fp32 partials,
 // which launch_gemm2_finish then sums.
 hipError_t launch_gemm2(const GemmArgs &a, int epi, const GemmPlan &plan, float *partial, hipStream_t s);
+// The same for plans with `big` set (rc_gemm3.hip): N a multiple of 144; a
+// folded LayerNorm's consumer takes u and v from fold_u and fold_v.
+hipError_t launch_gemm3(const GemmArgs &a, int epi, const GemmPlan &plan, float *partial, hipStream_t s);
+// u = W (1 + scale) and v = W shift for the MLP-up weights W [F][C] of up to
+// kLayers blocks: uv[l0 + l][0] = u, uv[l0 + l][1] = v, [F] each.
+struct FoldUvArgs {
+  static constexpr int kLayers = 32;
+  const void *w[kLayers];
+  const float *sst[kLayers];
+  const float *t0;
+  float *uv;
+  int l0, C, F, shift_row;
+};
+hipError_t launch_fold_uv(const FoldUvArgs &a, int layers, hipStream_t s);
 // Sum of a split plan's partials with the epilogue.  With `ln` non-null the
 // reduction of an EPI_RESID GEMM also applies `ln` (one pass over each
 // finished row); *ln_done tells the caller whether it did.

@@ -1,5 +1,5 @@
-"""Self-attention of one block at the edges of its tiles, splits and softmax
-range, through the block call, against the oracle."""
+"""One block at the edges of its kernels' tiles, splits and softmax range,
+through the block call, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -55,6 +55,16 @@ def test_edges(gh, gw, counts):
     the 128-query tiles, an empty chain."""
     print("self-attention", gh, gw, counts, flush=True)
     _block(gh, gw, counts, seed=gh + gw)
+
+
+@pytest.mark.parametrize("rows", [1009, 2449, 3969])
+def test_large_gemm_tiles(rows):
+    """Row counts that take the large GEMM tiles, each with a last row tile of
+    a few rows less than full: the MLP at 1009 rows (128x144 tiles, its
+    MLP-down split in four), QKV in 256x144 tiles at 2449, every GEMM at 3969
+    (256x288 tiles, one row short of a whole number of row blocks)."""
+    print("large tiles", rows, flush=True)
+    _block(64, 64, [rows], seed=rows)
 
 
 @pytest.mark.parametrize("sign", [1.0, -1.0])
