@@ -118,7 +118,7 @@ int part_cap_rows(int max_rows) { return kMaxSplits * std::min(max_rows, 1024); 
 struct WsLayout {
   size_t rows, offsets, X, A1, Q, O, G, part, ml, pmaps, e, th, temb, t0, gpart, fstats, fextra, fuv, total;
   size_t gpart_floats;
-  size_t txt_h, txt_y, txt_total;
+  size_t txt_h, txt_y, txt_part, txt_part_floats, txt_total;
 };
 
 WsLayout ws_layout(const rc_ctx *c, int max_rows, int B) {
@@ -152,6 +152,9 @@ WsLayout ws_layout(const rc_ctx *c, int max_rows, int B) {
   auto take2 = [&](size_t bytes) { size_t at = t; t = align256(t + bytes); return at; };
   w.txt_h = take2((size_t)B * c->M * c->C * c->esz);
   w.txt_y = take2((size_t)B * c->M * c->C * c->esz);
+  // split partials of the caption projection's first product (bf16)
+  w.txt_part_floats = c->esz == 2 && !c->cfg.token_mode ? (size_t)4 * B * c->M * c->C : 0;
+  w.txt_part = take2(w.txt_part_floats * 4);
   w.txt_total = t;
   return w;
 }
@@ -678,18 +681,35 @@ rc_status run_text(rc_ctx *c, const void *txt, int B, void *text_kv, void *ws, s
     rc::GemmArgs g{};
     g.A = txt; g.W = c->w.cap_w1; g.bias = c->w.cap_b1; g.M = B * M; g.N = C; g.K = c->cfg.text_dim;
     g.lda = c->cfg.text_dim; g.out = wsb + wl.txt_h; g.ldo = C;
-    RC_TRY(gemm<T>(c, RC_KC_GEMM, g, rc::EPI_GELU, nullptr, 0, s));
+    RC_TRY(gemm<T>(c, RC_KC_GEMM, g, rc::EPI_GELU, (float *)(wsb + wl.txt_part), wl.txt_part_floats, s));
     rc::GemmArgs g2{};
     g2.A = wsb + wl.txt_h; g2.W = c->w.cap_w2; g2.bias = c->w.cap_b2; g2.M = B * M; g2.N = C; g2.K = C;
     g2.lda = C; g2.out = wsb + wl.txt_y; g2.ldo = C;
     RC_TRY(gemm<T>(c, RC_KC_GEMM, g2, rc::EPI_STORE, nullptr, 0, s));
     y = wsb + wl.txt_y;
   }
+  rc::GemmArgs g{};
+  g.A = y; g.M = B * M; g.N = 2 * C; g.K = C; g.lda = C;
+  g.text_len = M; g.text_pad = c->Mp; g.tkv_chain_stride = (long long)text_kv_elems_per_entry(c); g.hidden = C;
+  const long long layer_stride = (long long)B * text_kv_elems_per_entry(c);
+  if (sizeof(T) == 2) {
+    for (int l0 = 0; l0 < c->L; l0 += rc::TextLayers::kLayers) {
+      rc::TextLayers tl{};
+      const int nl = std::min(c->L - l0, rc::TextLayers::kLayers);
+      for (int l = 0; l < nl; ++l) {
+        tl.w[l] = c->layers[l0 + l].xkv_w;
+        tl.b[l] = c->layers[l0 + l].xkv_b;
+      }
+      tl.layer_stride = layer_stride;
+      g.tkv = (T *)text_kv + l0 * layer_stride;
+      RC_TRY(timed(c, RC_KC_GEMM, s, [&] { return rc::launch_text_kv(g, tl, nl, s); }));
+    }
+    return RC_OK;
+  }
   for (int l = 0; l < c->L; ++l) {
-    rc::GemmArgs g{};
-    g.A = y; g.W = c->layers[l].xkv_w; g.bias = c->layers[l].xkv_b; g.M = B * M; g.N = 2 * C; g.K = C; g.lda = C;
-    g.tkv = (T *)text_kv + (size_t)l * B * text_kv_elems_per_entry(c);
-    g.text_len = M; g.text_pad = c->Mp; g.tkv_chain_stride = (long long)text_kv_elems_per_entry(c); g.hidden = C;
+    g.W = c->layers[l].xkv_w;
+    g.bias = c->layers[l].xkv_b;
+    g.tkv = (T *)text_kv + l * layer_stride;
     RC_TRY(gemm<T>(c, RC_KC_GEMM, g, rc::EPI_TEXTKV, nullptr, 0, s));
   }
   return RC_OK;

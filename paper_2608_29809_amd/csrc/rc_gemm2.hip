@@ -186,8 +186,9 @@ template <int W> __device__ __forceinline__ float group_sum(float v) {
   return v;
 }
 
+// The tile of workgroup p of T (see the order below).
 template <int BM, int BN, int STAGES, int KG, int WGM, int WGN, int EPI, bool SPLIT>
-__global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm2_kernel(GemmArgs g, float *partial, int k_per_split) {
+__device__ __forceinline__ void gemm2_tile(const GemmArgs &g, float *partial, int k_per_split, int p, int T) {
   constexpr int NW = WGM * WGN;                       // waves per K group
   constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 32, FN = WN / 32;
   constexpr int A_LD = BM * 8 / (64 * NW);            // direct loads per thread per stage (16 bytes each)
@@ -230,8 +231,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm2_kernel(GemmArgs g, 
   // group row tiles fastest, then column panels.  Consecutive logical tiles
   // run on one XCD, so the ~64 tiles in flight there share <= 16 row panels
   // of A and a few column panels of W in that XCD's L2.
-  const int tiles_m = gridDim.y, tiles_n = gridDim.x, TT = tiles_m * tiles_n, T = TT * gridDim.z;
-  const int p = blockIdx.x + tiles_n * (blockIdx.y + tiles_m * blockIdx.z);
+  const int tiles_m = gridDim.y, tiles_n = gridDim.x, TT = tiles_m * tiles_n;
   const int L = xcd_logical_id(p, T);
   const int kz = L / TT, r = L - kz * TT;
   constexpr int GM = 16;
@@ -564,6 +564,34 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm2_kernel(GemmArgs g, 
       }
     }
   }
+}
+
+template <int BM, int BN, int STAGES, int KG, int WGM, int WGN, int EPI, bool SPLIT>
+__global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm2_kernel(GemmArgs g, float *partial, int k_per_split) {
+  const int TT = gridDim.x * gridDim.y;
+  gemm2_tile<BM, BN, STAGES, KG, WGM, WGN, EPI, SPLIT>(g, partial, k_per_split,
+                                                       blockIdx.x + gridDim.x * blockIdx.y + TT * blockIdx.z,
+                                                       TT * gridDim.z);
+}
+
+// The text keys and values of up to kLayers blocks in one launch: block l of
+// the grid's z takes its own weights, bias and output entry.  One block's
+// product (120 rows per chain) fills 72 of the 256 CUs for 8.6 us and leaves
+// the chip between launches; all of them stream the weights once: 28 blocks
+// of one chain 240 -> 38 us.  128-row tiles hold a chain's 120 rows in one.
+__global__ __launch_bounds__(512) void text_kv_kernel(GemmArgs g, TextLayers t) {
+  g.W = t.w[blockIdx.z];
+  g.bias = t.b[blockIdx.z];
+  g.tkv = (bf16 *)g.tkv + blockIdx.z * t.layer_stride;
+  gemm2_tile<128, 128, 2, 1, 4, 2, EPI_TEXTKV, false>(g, nullptr, g.K, blockIdx.x + gridDim.x * blockIdx.y,
+                                                      gridDim.x * gridDim.y);
+}
+
+hipError_t launch_text_kv(const GemmArgs &a, const TextLayers &t, int layers, hipStream_t s) {
+  if (a.M <= 0 || layers <= 0) return hipSuccess;
+  if (layers > TextLayers::kLayers || a.N % 128 || a.hidden % 128 || a.K % G2_BK) return hipErrorInvalidValue;
+  rc_launch(text_kv_kernel, dim3(a.N / 128, (a.M + 127) / 128, layers), dim3(512), 0, s, a, t);
+  return hipGetLastError();
 }
 
 // Sum of the split partials in split order, then the epilogue.  One thread

@@ -156,6 +156,15 @@ struct FoldUvArgs {
 };
 hipError_t launch_fold_uv(const FoldUvArgs &a, int layers, hipStream_t s);
 // Sum of a split plan's partials with the epilogue.  With `ln` non-null the
+// Text keys and values (EPI_TEXTKV) of several blocks at once: W, bias and the
+// tkv entry of block l are w[l], b[l] and tkv + l * layer_stride elements.
+struct TextLayers {
+  static constexpr int kLayers = 32;
+  const void *w[kLayers];
+  const float *b[kLayers];
+  long long layer_stride;
+};
+hipError_t launch_text_kv(const GemmArgs &a, const TextLayers &t, int layers, hipStream_t s);
 // reduction of an EPI_RESID GEMM also applies `ln` (one pass over each
 // finished row); *ln_done tells the caller whether it did.
 hipError_t launch_gemm2_finish(const GemmArgs &a, int epi, const GemmPlan &plan, const float *partial,

@@ -85,3 +85,27 @@ def test_softmax_range(sign):
 
     print("softmax range", sign, flush=True)
     _block(16, 16, [200, 3], seed=5, edit=edit)
+
+
+@pytest.mark.parametrize("layers,batch", [(33, 1), (2, 3)])
+def test_text_of_all_blocks(layers, batch):
+    """The text keys and values that one launch writes for up to 32 blocks:
+    every block's own weights at its own place, a second launch past 32, rows
+    past a tile, zero padding."""
+    print("text", layers, batch, flush=True)
+    s = synth.ModelShape(layers=1, mlp=128, text_dim=1152, grid_h=8, grid_w=8, dtype="bf16", token_mode=True)
+    W = synth.make_weights(s, seed=3)
+    lw = W["layers"][0]
+    W["layers"] = [dict(lw, xkv_w=synth.bf16_round(lw["xkv_w"] * (1 + l / 64)), xkv_b=lw["xkv_b"] + l) for l in range(layers)]
+    s = synth.ModelShape(layers=layers, mlp=128, text_dim=1152, grid_h=8, grid_w=8, dtype="bf16", token_mode=True)
+    text = synth.make_text(s, batch, 4)
+    model = RegionCacheModel(s, W)
+    kv = model.prepare_text(model.to_storage(text)).view(torch.bfloat16).float().cpu().numpy()
+    kv = kv.reshape(layers, batch, 2, 16, 128 * 72)
+    for l in range(layers):
+        for b in range(batch):
+            k, v = (a.transpose(1, 0, 2) for a in O.text_kv(W["layers"][l], text[b], 16))  # [heads, tokens, 72]
+            gk, gv = kv[l, b, 0].reshape(16, 128, 72), kv[l, b, 1].reshape(16, 72, 128).transpose(0, 2, 1)
+            # one bf16 rounding of an fp32 sum of bf16 products
+            assert relerr(gk[:, :120], k) < 2.0 ** -8 and relerr(gv[:, :120], v) < 2.0 ** -8, (l, b)
+            assert not gk[:, 120:].any() and not gv[:, 120:].any()
