@@ -1097,9 +1097,8 @@ rc_status rc_localize_region(rc_ctx *c, const float *maps, int32_t batch, int32_
   RC_CHECK(device_present(), RC_ERR_NO_DEVICE, "no HIP device");
   hipStream_t s = (hipStream_t)stream;
   RC_TRY(timed(c, RC_KC_MISC, s, [&] {
-    return rc::launch_localize(maps, batch, c->cfg.grid_h, c->cfg.grid_w, n_delta, threshold, radius, mask, s);
+    return rc::launch_localize(maps, batch, c->cfg.grid_h, c->cfg.grid_w, n_delta, threshold, radius, mask, idx, offsets, s);
   }));
-  RC_TRY(timed(c, RC_KC_MISC, s, [&] { return rc::launch_compact(mask, batch, c->N, idx, offsets, s); }));
   if (offsets_host) {
     RC_HIP(hipMemcpyAsync(offsets_host, offsets, sizeof(int32_t) * (batch + 1), hipMemcpyDeviceToHost, s));
     RC_HIP(hipStreamSynchronize(s));

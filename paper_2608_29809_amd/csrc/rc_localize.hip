@@ -100,114 +100,219 @@ hipError_t launch_maps_from_logits(const uint16_t *logits, int n_layers, int hea
   return hipGetLastError();
 }
 
-// out[i] = sum_p partial[p][i] in order p = 0, 1, ...
-__global__ void sum_partials_kernel(const float *partial, int n_parts, int n, float *out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// out[i] = sum_p partial[p][i] in order p = 0, 1, ...  Latency-bound (2.8 MB
+// for 28 layers of 4096 x 6): sixteen partials are in flight per thread.
+__global__ __launch_bounds__(64) void sum_partials_kernel(const float *partial, int n_parts, int n, float *out) {
+  const int i = blockIdx.x * 64 + threadIdx.x;
   if (i >= n) return;
   float s = 0.0f;
-  for (int p = 0; p < n_parts; ++p) s += partial[(size_t)p * n + i];
+  constexpr int U = 16;
+  for (int p0 = 0; p0 < n_parts; p0 += U) {
+    float v[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) v[k] = partial[(size_t)min(p0 + k, n_parts - 1) * n + i];
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (p0 + k < n_parts) s += v[k];
+  }
   out[i] = s;
 }
 
 hipError_t launch_sum_partials(const float *partial, int n_parts, int n, float *out, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  rc_launch(sum_partials_kernel, dim3((n + 255) / 256), dim3(256), 0, s, partial, n_parts, n, out);
+  rc_launch(sum_partials_kernel, dim3((n + 63) / 64), dim3(64), 0, s, partial, n_parts, n, out);
   return hipGetLastError();
 }
 
-// One workgroup per chain: range of each delta map, threshold, union, dilation.
-__global__ __launch_bounds__(1024) void localize_kernel(const float *maps, int gh, int gw, int n_delta,
-                                                        float threshold, int radius, uint8_t *mask) {
-  extern __shared__ uint8_t sel[];
-  __shared__ float red_lo[16], red_hi[16];
-  const int b = blockIdx.x, tid = threadIdx.x, N = gh * gw;
-  const int lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
-  const float *m = maps + (size_t)b * N * n_delta;
-  for (int i = tid; i < N; i += blockDim.x) sel[i] = 0;
-  for (int j = 0; j < n_delta; ++j) {
-    float lo = INFINITY, hi = -INFINITY;
-    for (int i = tid; i < N; i += blockDim.x) {
-      const float v = m[(size_t)i * n_delta + j];
-      lo = fminf(lo, v);
-      hi = fmaxf(hi, v);
-    }
+// Stable compaction by a 1024-thread workgroup of up to 16 x 1024 tokens, of
+// which this thread holds i0 + 1024 k + tid for k < nk, selected where bit k
+// of `on` is set: their numbers go to idx[base ..] in ascending order.  One
+// ballot per 64 tokens, one scan over the counts of all of them; returns the
+// number selected.  cnt: [257] ints of LDS.
+__device__ __forceinline__ int compact_tokens(unsigned on, int nk, int i0, int base, int *idx, int *cnt) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t below = lane == 0 ? 0ull : ~0ull >> (64 - lane);
+  __syncthreads();  // earlier readers of cnt are done
+  for (int k = 0; k < nk; ++k) {
+    const uint64_t bal = __ballot((on >> k) & 1u);
+    if (lane == 0) cnt[k * 16 + wave] = __popcll(bal);
+  }
+  __syncthreads();
+  if (wave == 0) {  // exclusive scan of nk * 16 <= 256 counts, four per lane
+    int c[4], sum = 0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      lo = fminf(lo, __shfl_xor(lo, o, 64));
-      hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+    for (int e = 0; e < 4; ++e) {
+      c[e] = lane * 4 + e < nk * 16 ? cnt[lane * 4 + e] : 0;
+      sum += c[e];
     }
-    __syncthreads();
-    if (lane == 0) {
-      red_lo[wave] = lo;
-      red_hi[wave] = hi;
+    int inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += t;
     }
-    __syncthreads();
-    lo = red_lo[0];
-    hi = red_hi[0];
-    for (int w = 1; w < nw; ++w) {
-      lo = fminf(lo, red_lo[w]);
-      hi = fmaxf(hi, red_hi[w]);
+    int pre = inc - sum;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      cnt[lane * 4 + e] = pre;
+      pre += c[e];
     }
-    if (hi > lo) {
-      const float inv = 1.0f / (hi - lo);
-      for (int i = tid; i < N; i += blockDim.x)
-        if ((m[(size_t)i * n_delta + j] - lo) * inv >= threshold) sel[i] = 1;
+    if (lane == 63) cnt[256] = inc;
+  }
+  __syncthreads();
+  for (int k = 0; k < nk; ++k) {
+    const bool sel = (on >> k) & 1u;
+    const uint64_t bal = __ballot(sel);
+    if (sel) idx[base + cnt[k * 16 + wave] + __popcll(bal & below)] = i0 + k * 1024 + tid;
+  }
+  return cnt[256];
+}
+
+__device__ __forceinline__ float row16_fmin(float v) {
+  v = fminf(v, dpp_mov<0xB1>(v));
+  v = fminf(v, dpp_mov<0x4E>(v));
+  v = fminf(v, dpp_mov<0x141>(v));
+  return fminf(v, dpp_mov<0x140>(v));
+}
+
+// One workgroup per chain: range of each delta map, threshold, union,
+// dilation and, for a single chain (idx non-null), the compaction.
+//
+// Latency-bound (100 KB of maps at 64x64 tokens and six columns).  Every
+// column's range comes from one pass: a thread loads all columns of four
+// tokens before it uses any, and keeps them for the threshold where the chain
+// has no more than 4096 tokens.  The selection is a bit per token (the
+// ballots of the waves), so a token's neighbourhood is a shift of a word or
+// two per row.  With a pass over memory for each column's range and
+// another for its threshold the kernel took 25.8 us at 64x64 tokens and six
+// columns, and the compaction another 4.7.
+constexpr int kLocTok = 4;  // tokens of a thread loaded together
+__global__ __launch_bounds__(1024) void localize_kernel(const float *maps, int gh, int gw, int n_delta,
+                                                        float threshold, int radius, uint8_t *mask, int *idx,
+                                                        int *offsets) {
+  __shared__ uint64_t bits[258];       // selection of 64 tokens each, a spare word past the last
+  __shared__ float red[16][64], range[16];  // per column 2 j: minimum, 2 j + 1: -maximum
+  __shared__ int cnt[257];
+  const int b = blockIdx.x, tid = threadIdx.x, N = gh * gw;
+  const int lane = tid & 63, wave = tid >> 6;
+  const float *m = maps + (size_t)b * N * n_delta;
+  const int nk = (N + 1023) / 1024, n_chunk = (nk + kLocTok - 1) / kLocTok;
+  float v[kLocTok][8];
+  auto load = [&](int c) {
+#pragma unroll
+    for (int k = 0; k < kLocTok; ++k) {
+      const float *p = m + (size_t)min((c * kLocTok + k) * 1024 + tid, N - 1) * n_delta;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[k][j] = j < n_delta ? p[j] : 0.0f;
+    }
+  };
+  float lo[8], nhi[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) lo[j] = nhi[j] = INFINITY;
+  for (int c = 0; c < n_chunk; ++c) {
+    load(c);
+#pragma unroll
+    for (int k = 0; k < kLocTok; ++k)  // (a token past the last is the last again)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        lo[j] = fminf(lo[j], v[k][j]);
+        nhi[j] = fminf(nhi[j], -v[k][j]);
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    lo[j] = row16_fmin(lo[j]);
+    nhi[j] = row16_fmin(nhi[j]);
+    if ((lane & 15) == 0) {
+      red[2 * j][wave * 4 + (lane >> 4)] = lo[j];
+      red[2 * j + 1][wave * 4 + (lane >> 4)] = nhi[j];
     }
   }
   __syncthreads();
-  for (int i = tid; i < N; i += blockDim.x) {
-    const int y = i / gw, x = i - (i / gw) * gw;
-    uint8_t on = 0;
-    for (int dy = -radius; dy <= radius && !on; ++dy) {
-      const int yy = y + dy;
-      if (yy < 0 || yy >= gh) continue;
-      for (int dx = -radius; dx <= radius; ++dx) {
-        const int xx = x + dx;
-        if (xx >= 0 && xx < gw && sel[yy * gw + xx]) {
-          on = 1;
-          break;
-        }
-      }
+  {
+    float r = red[wave][lane];
+    r = row16_fmin(r);
+    r = fminf(r, __shfl_xor(r, 16, 64));
+    r = fminf(r, __shfl_xor(r, 32, 64));
+    if (lane == 0) range[wave] = r;
+  }
+  __syncthreads();
+  unsigned live = 0;  // columns that select (a constant map selects nothing)
+  float inv[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    lo[j] = range[2 * j];
+    const float hi = -range[2 * j + 1];
+    live |= (unsigned)(j < n_delta && hi > lo[j]) << j;
+    inv[j] = 1.0f / (hi - lo[j]);
+  }
+  for (int c = 0; c < n_chunk; ++c) {
+    if (n_chunk > 1) load(c);
+#pragma unroll
+    for (int k = 0; k < kLocTok; ++k) {
+      const int i = (c * kLocTok + k) * 1024 + tid;
+      bool on = false;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) on = on || (((live >> j) & 1u) && (v[k][j] - lo[j]) * inv[j] >= threshold);
+      const uint64_t bal = __ballot(on && i < N);
+      if (lane == 0 && i < N) bits[i >> 6] = bal;
     }
-    mask[(size_t)b * N + i] = on;
+  }
+  if (tid == 0) bits[N >> 6] = 0;
+  __syncthreads();
+  unsigned sel = 0;
+  for (int k = 0; k < nk; ++k) {
+    const int i = k * 1024 + tid;
+    if (i < N) {
+      const int y = i / gw, x = i - y * gw;
+      const int x0 = max(x - radius, 0), w = min(x + radius, gw - 1) - x0 + 1;
+      const int y0 = max(y - radius, 0), y1 = min(y + radius, gh - 1);
+      uint64_t any = 0;
+      for (int yy = y0; yy <= y1; ++yy) {
+        const int p = yy * gw + x0, sh = p & 63;
+        uint64_t f = bits[p >> 6] >> sh;
+        if (sh) f |= bits[(p >> 6) + 1] << (64 - sh);
+        any |= f;
+      }
+      const unsigned on = (any & ((1ull << w) - 1)) != 0;
+      sel |= on << k;
+      mask[(size_t)b * N + i] = (uint8_t)on;
+    }
+  }
+  if (idx) {
+    const int total = compact_tokens(sel, nk, 0, 0, idx, cnt);
+    if (tid == 0) {
+      offsets[0] = 0;
+      offsets[1] = total;
+    }
   }
 }
 
 hipError_t launch_localize(const float *maps, int B, int gh, int gw, int n_delta, float threshold, int radius,
-                           uint8_t *mask, hipStream_t s) {
-  rc_launch(localize_kernel, dim3(B), dim3(1024), (size_t)gh * gw, s, maps, gh, gw, n_delta, threshold,
-                     radius, mask);
-  return hipGetLastError();
+                           uint8_t *mask, int *idx, int *offsets, hipStream_t s) {
+  if ((long)gh * gw > 16384 || (gh * gw) % 64 || n_delta > 8) return hipErrorInvalidValue;
+  int *one = B == 1 ? idx : nullptr;
+  rc_launch(localize_kernel, dim3(B), dim3(1024), 0, s, maps, gh, gw, n_delta, threshold, radius, mask, one, offsets);
+  return B == 1 ? hipGetLastError() : launch_compact(mask, B, gh * gw, idx, offsets, s);
 }
 
-// Single-workgroup stable compaction over all chains: per 1024-token chunk a
-// ballot/popcount prefix within each wave plus an LDS prefix over waves.
+// Stable compaction over all chains by one workgroup, up to 16384 tokens of a
+// chain at a time (every mask byte of them is loaded before the first is used).
 __global__ __launch_bounds__(1024) void compact_kernel(const uint8_t *mask, int B, int N, int *idx, int *offsets) {
-  __shared__ int wave_tot[16];
-  __shared__ int wave_pre[16];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ int cnt[257];
+  const int tid = threadIdx.x;
   int base = 0;
   for (int b = 0; b < B; ++b) {
     if (tid == 0) offsets[b] = base;
-    for (int i0 = 0; i0 < N; i0 += 1024) {
-      const int i = i0 + tid;
-      const bool on = i < N && mask[(size_t)b * N + i] != 0;
-      const uint64_t bal = __ballot(on);
-      const int within = __popcll(bal & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
-      if (lane == 0) wave_tot[wave] = __popcll(bal);
-      __syncthreads();
-      if (tid == 0) {
-        int acc = 0;
-        for (int w = 0; w < 16; ++w) {
-          wave_pre[w] = acc;
-          acc += wave_tot[w];
-        }
-        wave_tot[0] = acc;  // chunk total
+    for (int i0 = 0; i0 < N; i0 += 16384) {
+      const int nk = min(16, (N - i0 + 1023) / 1024);
+      unsigned on = 0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const int i = i0 + k * 1024 + tid;
+        on |= (unsigned)(i < N && mask[(size_t)b * N + min(i, N - 1)] != 0) << k;
       }
-      __syncthreads();
-      if (on) idx[base + wave_pre[wave] + within] = i;
-      base += wave_tot[0];
-      __syncthreads();
+      base += compact_tokens(on, nk, i0, base, idx, cnt);
     }
   }
   if (tid == 0) offsets[B] = base;
