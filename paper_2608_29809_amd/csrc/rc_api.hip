@@ -277,7 +277,7 @@ rc_status gemm(rc_ctx *c, int cls, const rc::GemmArgs &g, int epi, float *part, 
     if (pl.splits == 1) return RC_OK;
     return timed(c, RC_KC_SPLIT_FINISH, s, [&] { return rc::launch_gemm2_finish(g, epi, pl, part, s, ln, ln_done); });
   } else {
-    return timed(c, cls, s, [&] { return rc::launch_gemm<T>(g, epi, s); });
+    return timed(c, cls, s, [&] { return rc::launch_gemm_f32(g, epi, s); });
   }
 }
 

@@ -1,194 +1,171 @@
-// Matrix-core GEMM over ragged active-row sets: Y[M][N] = A[M][K] . W[N][K]^T
-// with fused epilogues.  The QKV epilogue writes fresh active keys and values
-// straight to their token positions in the cache slot (the fusion of
+// float32 GEMM over ragged active-row sets: Y[M][N] = A[M][K] . W[N][K]^T with
+// fused epilogues (rc_internal.h).  The QKV epilogue writes fresh active keys
+// and values straight to their token positions in the cache slot (the fusion of
 // Sec. 3.4, "Kernel Fusing"), and the residual epilogue can scatter the
 // merged hidden state into the cached H (Sec. 3.3 merge).
 //
-// Tiling: 256 threads = 4 waves arranged 2x2; a BMxBN tile with a K step of
-// 128 bytes per row (64 bf16 or 32 f32).  Each wave owns a (BM/2)x(BN/2)
-// sub-tile made of 32x32 MFMA blocks.  Operands go global -> registers ->
-// LDS (rows padded by 16 bytes) with the next K step's global loads issued
-// before the current step's MFMAs.
+// 32-row tiles whose four waves each hold the whole tile and take a quarter
+// of every K stage: LDS reads are two per eight MFMAs of 64 clocks, small
+// grids get many workgroups, and the float32 matrix rate (157 TFLOP/s) or, at
+// a few hundred rows, the first weights' latency is what is left.  64-wide
+// stages stream through a ring of direct copies, two workgroups per CU.
+// Against register-staged 64x64 to 128x128 tiles of 2x2 waves: at 154 rows
+// 59.6 -> 9.3 us (1152 x 1152) and 230 -> 31 (MLP-down); at 4096 rows MLP-up
+// 457 -> 414, QKV 409 -> 315, MLP-down 779 -> 404.
+//
+// Ring rows are 256 bytes, their sixteen 16-byte chunks XOR-swizzled by row &
+// 15 (16 rows of a fragment read touch every bank once).  A lane's 16 bytes
+// are four k of its operand row, used one per 32x32x2 MFMA: instruction e
+// multiplies k = e of the lower half-wave and k = 4 + e of the upper one, the
+// same pairs in A and W.  The waves' partial tiles are summed in wave order.
 #include "rc_common.h"
 #include "rc_launch.h"
 #include "rc_internal.h"
 
 namespace rc {
 
-template <typename T, int BM, int BN, int EPI>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
-  constexpr int VE = 16 / sizeof(T);      // elements per 16-byte chunk
-  constexpr int KT = 128 / sizeof(T);     // K step in elements
-  constexpr int LDS_LD = KT + VE;         // padded LDS row (elements)
-  constexpr int CPR = KT / VE;            // 16-byte chunks per tile row (8)
-  constexpr int A_CH = BM * CPR / 256;    // chunks per thread
-  constexpr int B_CH = BN * CPR / 256;
-  constexpr int WM = BM / 2, WN = BN / 2; // wave sub-tile
-  constexpr int FM = WM / 32, FN = WN / 32;
-  constexpr int KS = Mfma<T>::KS;
-  typedef typename Mfma<T>::frag frag;
+constexpr int GF_S = 3, GF_BM = 32, GF_K = 64;
 
-  __shared__ __attribute__((aligned(16))) T As[BM * LDS_LD];
-  __shared__ __attribute__((aligned(16))) T Bs[BN * LDS_LD];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const T *A = (const T *)g.A;
-  const T *W = (const T *)g.W;
-
-  V16 ra[A_CH], rb[B_CH];
-  auto load = [&](int k0) {
+template <int BN, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
+  constexpr int FN = BN / 32, ROWS = GF_BM + BN, STAGE = ROWS * GF_K * 4;
+  constexpr int AC = GF_BM * 256 / 4096, NL = ROWS * 256 / 4096;  // copies per wave: A rows', all
+  constexpr int CLD = BN + 4;
+  static_assert(4 * GF_BM * CLD * 4 <= GF_S * STAGE, "the partial tiles fit the ring");
+  __shared__ __attribute__((aligned(1024))) char lds[GF_S * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g32 = lane >> 5, r32 = lane & 31;
+  // column panels share an XCD's L2: the row tiles of a panel are consecutive
+  const int T = gridDim.x * gridDim.y, L = xcd_logical_id(blockIdx.x + gridDim.x * blockIdx.y, T);
+  const int m0 = (L % gridDim.y) * GF_BM, n0 = (L / gridDim.y) * BN;
+  const float *A = (const float *)g.A, *W = (const float *)g.W;
+  const int nk = g.K / GF_K;
+  const float *src[NL];
 #pragma unroll
-    for (int c = 0; c < A_CH; ++c) {
-      int ch = tid + c * 256, r = ch / CPR, col = (ch % CPR) * VE;
-      int gr = m0 + r;
-      if (gr < g.M) ra[c] = *(const V16 *)(A + (size_t)gr * g.lda + k0 + col);
-      else ra[c] = V16{{0u, 0u, 0u, 0u}};
-    }
+  for (int i = 0; i < NL; ++i) {
+    const int row = (i * 4 + wave) * 4 + (lane >> 4), c = (lane & 15) ^ (row & 15);
+    src[i] = (i < AC ? A + (size_t)min(m0 + row, g.M - 1) * g.lda : W + (size_t)(n0 + row - GF_BM) * g.K) + c * 4;
+  }
+  auto issue = [&](int slot, int kt) {
 #pragma unroll
-    for (int c = 0; c < B_CH; ++c) {
-      int ch = tid + c * 256, r = ch / CPR, col = (ch % CPR) * VE;
-      rb[c] = *(const V16 *)(W + (size_t)(n0 + r) * g.K + k0 + col);
-    }
+    for (int i = 0; i < NL; ++i) lds_dma16(src[i] + kt * GF_K, lds + slot * STAGE + (i * 4 + wave) * 1024);
   };
-  auto store = [&]() {
+  f32x16 acc[FN];
 #pragma unroll
-    for (int c = 0; c < A_CH; ++c) {
-      int ch = tid + c * 256, r = ch / CPR, col = (ch % CPR) * VE;
-      *(V16 *)(As + r * LDS_LD + col) = ra[c];
-    }
+  for (int j = 0; j < FN; ++j)
 #pragma unroll
-    for (int c = 0; c < B_CH; ++c) {
-      int ch = tid + c * 256, r = ch / CPR, col = (ch % CPR) * VE;
-      *(V16 *)(Bs + r * LDS_LD + col) = rb[c];
-    }
-  };
-
-  f32x16 acc[FM][FN];
+    for (int e = 0; e < 16; ++e) acc[j][e] = 0.0f;
 #pragma unroll
-  for (int i = 0; i < FM; ++i)
+  for (int s = 0; s < GF_S - 1; ++s)
+    if (s < nk) issue(s, s);
+  for (int kt = 0, slot = 0; kt < nk; ++kt, slot = slot == GF_S - 1 ? 0 : slot + 1) {
+    if (kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // (the last stage's fragments have been multiplied: its slot is free past the barrier)
+    asm volatile("s_barrier" ::: "memory");
+    if (kt + GF_S - 1 < nk) issue(slot == 0 ? GF_S - 1 : slot - 1, kt + GF_S - 1);
+    const char *st = lds + slot * STAGE;
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
+    for (int q = 0; q < 2; ++q) {
+      const int c = ((wave * 4 + q * 2 + g32) ^ (r32 & 15)) << 4;
+      const f32x4 a = *(const f32x4 *)(st + r32 * 256 + c);
+      f32x4 b[FN];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-  const int nk = g.K / KT;
-  load(0);
-  store();
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) load((kt + 1) * KT);
+      for (int j = 0; j < FN; ++j) b[j] = *(const f32x4 *)(st + (GF_BM + j * 32 + r32) * 256 + c);
 #pragma unroll
-    for (int kk = 0; kk < KT / (2 * KS); ++kk) {
-      const int kc = kk * 2 * KS + (lane >> 5) * KS;
-      frag a[FM], b[FN];
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
-        a[i] = *(const frag *)(As + (wm * WM + i * 32 + (lane & 31)) * LDS_LD + kc);
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-        b[j] = *(const frag *)(Bs + (wn * WN + j * 32 + (lane & 31)) * LDS_LD + kc);
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = Mfma<T>::mma(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-    if (kt + 1 < nk) {
-      store();
-      __syncthreads();
+        for (int j = 0; j < FN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[j][e], acc[j], 0, 0, 0);
     }
   }
+  __syncthreads();
+  float *ct = (float *)lds + wave * GF_BM * CLD;
+#pragma unroll
+  for (int j = 0; j < FN; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) ct[((e >> 2) * 8 + g32 * 4 + (e & 3)) * CLD + j * 32 + r32] = acc[j][e];
+  __syncthreads();
 
-  // ---------------------------------------------------------------- epilogue
+  constexpr int IT = GF_BM * BN / 4 / 256;
+  const int col = (tid % (BN / 4)) * 4, n = n0 + col, row0 = tid / (BN / 4);
+  constexpr int RSTEP = 1024 / BN;
+  f32x4 bb = f32x4{0.0f, 0.0f, 0.0f, 0.0f}, gt = bb + 1.0f;
+  if (g.bias) bb = *(const f32x4 *)(g.bias + n);
+  if (EPI == EPI_RESID && g.gate) gt = *(const f32x4 *)(g.gate + n);
+  if (EPI == EPI_RESID && g.gate && g.gate2) gt += *(const f32x4 *)(g.gate2 + n);
+  int part = 0, hh = 0, dd = 0;
+  if (EPI == EPI_QKV || EPI == EPI_TEXTKV) {
+    part = n / g.hidden;
+    const int c = n - part * g.hidden;
+    hh = c / kHeadDim;
+    dd = c - hh * kHeadDim;
+  }
 #pragma unroll
-  for (int j = 0; j < FN; ++j) {
-    const int n = n0 + wn * WN + j * 32 + (lane & 31);
-    const float bn = g.bias ? g.bias[n] : 0.0f;
-    float gate = 1.0f;
-    if (EPI == EPI_RESID && g.gate) gate = g.gate[n] + (g.gate2 ? g.gate2[n] : 0.0f);
-    int part = 0, hh = 0, dd = 0;
-    if (EPI == EPI_QKV || EPI == EPI_TEXTKV) {
-      part = n / g.hidden;
-      int c = n - part * g.hidden;
-      hh = c / kHeadDim;
-      dd = c - hh * kHeadDim;
-    }
+  for (int it = 0; it < IT; ++it) {
+    const int row = row0 + it * RSTEP, m = m0 + row;
+    if (m >= g.M) continue;
+    f32x4 v = bb * 0.0f;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
+    for (int w = 0; w < 4; ++w) v += *(const f32x4 *)((const float *)lds + (w * GF_BM + row) * CLD + col);
+    v += bb;
+    if (EPI == EPI_STORE) {
+      *(f32x4 *)((float *)g.out + (size_t)m * g.ldo + n) = v;
+    } else if (EPI == EPI_GELU) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = m0 + wm * WM + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-        if (m >= g.M) continue;
-        const float v = acc[i][j][e] + bn;
-        if (EPI == EPI_STORE) {
-          ((T *)g.out)[(size_t)m * g.ldo + n] = from_f<T>(v);
-        } else if (EPI == EPI_GELU) {
-          ((T *)g.out)[(size_t)m * g.ldo + n] = from_f<T>(gelu_tanh(v));
-        } else if (EPI == EPI_RESID) {
-          float *xp = g.X + (size_t)m * g.ldx + n;
-          const float x = *xp + gate * v;
-          *xp = x;
-          if (g.xt) ((T *)g.xt)[(size_t)m * g.ldx + n] = from_f<T>(x);
-          if (g.hrows) ((T *)g.hrows)[(size_t)m * g.N + n] = from_f<T>(x);
-          if (g.hslot) {
-            const int pk = g.rows[m];
-            ((T *)g.hslot)[row_chain(pk) * g.chain_stride + (size_t)row_token(pk) * g.hidden + n] =
-                from_f<T>(x);
-          }
-        } else if (EPI == EPI_QKV) {
-          if (part == 0) {
-            ((T *)g.out)[(size_t)m * g.ldo + n] = from_f<T>(v);
-          } else {
-            const int pk = g.rows[m];
-            const size_t cb = (size_t)row_chain(pk) * g.chain_stride;
-            const int tok = row_token(pk);
-            if (part == 1)
-              ((T *)g.kslot)[cb + ((size_t)hh * g.tokens + tok) * kHeadDim + dd] = from_f<T>(v);
-            else
-              ((T *)g.vslot)[cb + ((size_t)hh * g.tokens + tok) * kHeadDim + dd] = from_f<T>(v);
-          }
-        } else if (EPI == EPI_TEXTKV) {
-          const int b = m / g.text_len, t = m - b * g.text_len;
-          T *base = (T *)g.tkv + (size_t)b * g.tkv_chain_stride;
-          const size_t half = (size_t)(g.hidden / kHeadDim) * g.text_pad * kHeadDim;
-          if (part == 0)
-            base[((size_t)hh * g.text_pad + t) * kHeadDim + dd] = from_f<T>(v);
-          else
-            base[half + ((size_t)hh * kHeadDim + dd) * g.text_pad + t] = from_f<T>(v);
-        }
+      for (int q = 0; q < 4; ++q) v[q] = gelu_tanh(v[q]);
+      *(f32x4 *)((float *)g.out + (size_t)m * g.ldo + n) = v;
+    } else if (EPI == EPI_RESID) {
+      f32x4 *xp = (f32x4 *)(g.X + (size_t)m * g.ldx + n);
+      v = *xp + gt * v;
+      *xp = v;
+      if (g.xt) *(f32x4 *)((float *)g.xt + (size_t)m * g.ldx + n) = v;
+      if (g.hrows) *(f32x4 *)((float *)g.hrows + (size_t)m * g.N + n) = v;
+      if (g.hslot) {
+        const int pk = g.rows[m];
+        *(f32x4 *)((float *)g.hslot + row_chain(pk) * g.chain_stride + (size_t)row_token(pk) * g.hidden + n) = v;
+      }
+    } else if (EPI == EPI_QKV) {
+      if (part == 0) {
+        *(f32x4 *)((float *)g.out + (size_t)m * g.ldo + n) = v;
+      } else {
+        const int pk = g.rows[m];
+        *(f32x4 *)((float *)(part == 1 ? g.kslot : g.vslot) + (size_t)row_chain(pk) * g.chain_stride +
+                   ((size_t)hh * g.tokens + row_token(pk)) * kHeadDim + dd) = v;
+      }
+    } else if (EPI == EPI_TEXTKV) {
+      const int b = m / g.text_len, t = m - b * g.text_len;
+      float *base = (float *)g.tkv + (size_t)b * g.tkv_chain_stride;
+      const size_t half = (size_t)(g.hidden / kHeadDim) * g.text_pad * kHeadDim;
+      if (part == 0) {
+        *(f32x4 *)(base + ((size_t)hh * g.text_pad + t) * kHeadDim + dd) = v;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) base[half + ((size_t)hh * kHeadDim + dd + q) * g.text_pad + t] = v[q];
       }
     }
   }
 }
 
-template <typename T, int BM, int BN>
-static hipError_t launch_tile(const GemmArgs &a, int epi, hipStream_t s) {
-  dim3 grid(a.N / BN, (a.M + BM - 1) / BM);
+template <int BN> static hipError_t launch_f32(const GemmArgs &a, int epi, hipStream_t s) {
+  const dim3 grid(a.N / BN, (a.M + GF_BM - 1) / GF_BM), block(256);
   switch (epi) {
-    case EPI_STORE: rc_launch(gemm_kernel<T, BM, BN, EPI_STORE>, grid, dim3(256), 0, s, a); break;
-    case EPI_GELU: rc_launch(gemm_kernel<T, BM, BN, EPI_GELU>, grid, dim3(256), 0, s, a); break;
-    case EPI_RESID: rc_launch(gemm_kernel<T, BM, BN, EPI_RESID>, grid, dim3(256), 0, s, a); break;
-    case EPI_QKV: rc_launch(gemm_kernel<T, BM, BN, EPI_QKV>, grid, dim3(256), 0, s, a); break;
-    case EPI_TEXTKV: rc_launch(gemm_kernel<T, BM, BN, EPI_TEXTKV>, grid, dim3(256), 0, s, a); break;
+    case EPI_STORE: rc_launch(gemm_f32_kernel<BN, EPI_STORE>, grid, block, 0, s, a); break;
+    case EPI_GELU: rc_launch(gemm_f32_kernel<BN, EPI_GELU>, grid, block, 0, s, a); break;
+    case EPI_RESID: rc_launch(gemm_f32_kernel<BN, EPI_RESID>, grid, block, 0, s, a); break;
+    case EPI_QKV: rc_launch(gemm_f32_kernel<BN, EPI_QKV>, grid, block, 0, s, a); break;
+    case EPI_TEXTKV: rc_launch(gemm_f32_kernel<BN, EPI_TEXTKV>, grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// Tile choice: the largest tile that still gives every CU at least two
-// workgroups, falling back to 64x64 for the narrow low-row GEMMs.
-template <typename T> hipError_t launch_gemm(const GemmArgs &a, int epi, hipStream_t s) {
+// Tile choice: 32x64 tiles, 32x32 below 200 of them (they halve a workgroup's
+// share of the weights: 9.5 against 13 us at 154 x 1152 x 1152).
+hipError_t launch_gemm_f32(const GemmArgs &a, int epi, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  if (a.N % 64 != 0 || a.K % (128 / (int)sizeof(T)) != 0) return hipErrorInvalidValue;
-  auto wgs = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * (a.N / bn); };
-  if (a.N % 128 == 0 && wgs(128, 128) >= 512) return launch_tile<T, 128, 128>(a, epi, s);
-  if (a.N % 128 == 0 && wgs(64, 128) >= 384) return launch_tile<T, 64, 128>(a, epi, s);
-  return launch_tile<T, 64, 64>(a, epi, s);
+  if (a.N % 64 != 0 || a.K % GF_K != 0) return hipErrorInvalidValue;
+  const long wgs = (long)((a.M + GF_BM - 1) / GF_BM) * (a.N / 64);
+  return wgs >= 200 ? launch_f32<64>(a, epi, s) : launch_f32<32>(a, epi, s);
 }
-
-template hipError_t launch_gemm<bf16>(const GemmArgs &, int, hipStream_t);
-template hipError_t launch_gemm<float>(const GemmArgs &, int, hipStream_t);
 
 }  // namespace rc

@@ -116,7 +116,8 @@ __device__ __forceinline__ int2 chain_rows(const AttnArgs &a, int b) {
   return make_int2(a.offsets[b], a.offsets[b + 1]);
 }
 
-template <typename T> hipError_t launch_gemm(const GemmArgs &a, int epi, hipStream_t s);
+// float32 GEMM (rc_gemm.hip).
+hipError_t launch_gemm_f32(const GemmArgs &a, int epi, hipStream_t s);
 
 // bf16 GEMM with direct-to-LDS staging and optional split-K (rc_gemm2.hip).
 struct GemmPlan {
@@ -155,7 +156,6 @@ struct FoldUvArgs {
   int l0, C, F, shift_row;
 };
 hipError_t launch_fold_uv(const FoldUvArgs &a, int layers, hipStream_t s);
-// Sum of a split plan's partials with the epilogue.  With `ln` non-null the
 // Text keys and values (EPI_TEXTKV) of several blocks at once: W, bias and the
 // tkv entry of block l are w[l], b[l] and tkv + l * layer_stride elements.
 struct TextLayers {
@@ -165,6 +165,7 @@ struct TextLayers {
   long long layer_stride;
 };
 hipError_t launch_text_kv(const GemmArgs &a, const TextLayers &t, int layers, hipStream_t s);
+// Sum of a split plan's partials with the epilogue.  With `ln` non-null the
 // reduction of an EPI_RESID GEMM also applies `ln` (one pass over each
 // finished row); *ln_done tells the caller whether it did.
 hipError_t launch_gemm2_finish(const GemmArgs &a, int epi, const GemmPlan &plan, const float *partial,
