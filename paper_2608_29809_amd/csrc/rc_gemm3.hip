@@ -411,39 +411,63 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, 2) void gemm3_kernel(GemmArgs 
 }
 
 // u = W (1 + scale) and v = W shift of a folded LayerNorm, for every block of
-// a step: one wave per output row n of W [F][C] (fp32 sums over the bf16
-// weights).  grid (F / 4, layers).
+// a step (fp32 sums over the bf16 weights).  A workgroup holds 1 + scale and
+// shift in LDS and takes 32 rows of W, eight per wave, all loaded before the
+// first is used: bound by the weights' bytes (14 us for four blocks' 42 MB;
+// 22.9 with a row per wave, which reads the two vectors again for each row).
+constexpr int UV_ROWS = 32;
 __global__ __launch_bounds__(256) void fold_uv_kernel(FoldUvArgs a) {
-  const int l = blockIdx.y, n = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const bf16 *w = (const bf16 *)a.w[l] + (size_t)n * a.C;
-  const float *sst = a.sst[l];
-  float u = 0.0f, v = 0.0f;
-  for (int k = lane * 8; k < a.C; k += 512) {
-    const bf16x8 wv = *(const bf16x8 *)(w + k);
+  constexpr int RW = UV_ROWS / 4, MAXC = 3;  // rows per wave; C <= 512 MAXC
+  __shared__ float sc[512 * MAXC], sh[512 * MAXC];
+  const int l = blockIdx.y, tid = threadIdx.x, lane = tid & 63, n0 = blockIdx.x * UV_ROWS + (tid >> 6) * RW;
+  bf16x8 w[RW][MAXC];
 #pragma unroll
-    for (int q = 0; q < 8; q += 4) {
-      const f32x4 sh = *(const f32x4 *)(sst + (size_t)a.shift_row * a.C + k + q) + *(const f32x4 *)(a.t0 + (size_t)a.shift_row * a.C + k + q);
-      const f32x4 sc = 1.0f + *(const f32x4 *)(sst + (size_t)(a.shift_row + 1) * a.C + k + q) +
-                       *(const f32x4 *)(a.t0 + (size_t)(a.shift_row + 1) * a.C + k + q);
+  for (int r = 0; r < RW; ++r) {
+    const bf16 *row = (const bf16 *)a.w[l] + (size_t)(n0 + r) * a.C;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        u += (float)wv[q + e] * sc[e];
-        v += (float)wv[q + e] * sh[e];
-      }
+    for (int i = 0; i < MAXC; ++i) {
+      const int k = (lane + 64 * i) * 8;
+      w[r][i] = Mfma<bf16>::zero();
+      if (k < a.C) w[r][i] = *(const bf16x8 *)(row + k);
     }
   }
-  u = wave_sum(u);
-  v = wave_sum(v);
-  if (lane == 0) {
-    a.uv[((size_t)(a.l0 + l) * 2) * a.F + n] = u;
-    a.uv[((size_t)(a.l0 + l) * 2 + 1) * a.F + n] = v;
+  const float *sst = a.sst[l] + (size_t)a.shift_row * a.C, *t0 = a.t0 + (size_t)a.shift_row * a.C;
+  for (int k = tid; k < 512 * MAXC; k += 256) {
+    sh[k] = k < a.C ? sst[k] + t0[k] : 0.0f;
+    sc[k] = k < a.C ? 1.0f + sst[a.C + k] + t0[a.C + k] : 0.0f;
+  }
+  __syncthreads();
+  float u[RW], v[RW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r) u[r] = v[r] = 0.0f;
+#pragma unroll
+  for (int i = 0; i < MAXC; ++i)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int k = (lane + 64 * i) * 8 + q;
+      const float s = sc[k], t = sh[k];
+#pragma unroll
+      for (int r = 0; r < RW; ++r) {
+        u[r] += (float)w[r][i][q] * s;
+        v[r] += (float)w[r][i][q] * t;
+      }
+    }
+  float *out = a.uv + (size_t)(a.l0 + l) * 2 * a.F;
+#pragma unroll
+  for (int r = 0; r < RW; ++r) {
+    u[r] = wave_sum(u[r]);
+    v[r] = wave_sum(v[r]);
+    if (lane == 0) {
+      out[n0 + r] = u[r];
+      out[a.F + n0 + r] = v[r];
+    }
   }
 }
 
 hipError_t launch_fold_uv(const FoldUvArgs &a, int layers, hipStream_t s) {
   if (layers <= 0) return hipSuccess;
-  if (layers > FoldUvArgs::kLayers || a.F % 4 || a.C % 8) return hipErrorInvalidValue;
-  rc_launch(fold_uv_kernel, dim3(a.F / 4, layers), dim3(256), 0, s, a);
+  if (layers > FoldUvArgs::kLayers || a.F % UV_ROWS || a.C % 8 || a.C > 1536) return hipErrorInvalidValue;
+  rc_launch(fold_uv_kernel, dim3(a.F / UV_ROWS, layers), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
