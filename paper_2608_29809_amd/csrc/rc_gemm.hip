@@ -159,13 +159,15 @@ template <int BN> static hipError_t launch_f32(const GemmArgs &a, int epi, hipSt
   return hipGetLastError();
 }
 
-// Tile choice: 32x64 tiles, 32x32 below 200 of them (they halve a workgroup's
-// share of the weights: 9.5 against 13 us at 154 x 1152 x 1152).
+// Tile choice: the tile whose fullest CU has the least to do (a 32x64 tile
+// is two 32x32 ones), 32x64 where they are equal (half the A traffic).  At 154
+// rows QKV is 270 of the 32x64 tiles, two on some CUs and one on most: 26.5 us,
+// 22 with 540 of 32x32.
 hipError_t launch_gemm_f32(const GemmArgs &a, int epi, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   if (a.N % 64 != 0 || a.K % GF_K != 0) return hipErrorInvalidValue;
-  const long wgs = (long)((a.M + GF_BM - 1) / GF_BM) * (a.N / 64);
-  return wgs >= 200 ? launch_f32<64>(a, epi, s) : launch_f32<32>(a, epi, s);
+  const long w64 = (long)((a.M + GF_BM - 1) / GF_BM) * (a.N / 64);
+  return (w64 + 255) / 256 * 2 <= (2 * w64 + 255) / 256 ? launch_f32<64>(a, epi, s) : launch_f32<32>(a, epi, s);
 }
 
 }  // namespace rc
