@@ -477,6 +477,16 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
       splits *= 2;
   }
 
+  // cross-attention query (bf16): by a GEMM of its own where the fused
+  // kernel, one workgroup of 64 rows of a head per CU, would take more than
+  // one round of about 11.5 us (fused against projection + attention: 723 rows,
+  // one round, 13 us for either, a launch more; 1639 rows 23.4 against
+  // 12.0 + 9.4, 2458 rows 35 against 15.5 + 10.9, 4096 46 against 16.5 + 12.7,
+  // 16384 170 against 46 + 42.6)
+  long xq_wgs = 0;
+  for (int b = 0; b < B; ++b) xq_wgs += (long)(counts[b] + 63) / 64 * H;
+  const bool xq_gemm = sizeof(T) == 2 && xq_wgs > 256;
+
   const bool emit = io->maps && io->n_delta > 0;
   // device pool: slot (b, step, l) in place; host-resident pool: entry
   // l % kRing of the staging ring, chains one slot apart
@@ -557,7 +567,7 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
       g.warm = lw.xproj_w; g.warm_lines = wlines(C, C);
       RC_TRY(gemm<T>(c, RC_KC_GEMM_PROJ, g, rc::EPI_RESID, gpart, gpf, s));
     }
-    if (sizeof(T) != 2) {  // cross-attention query (bf16: projected inside the cross-attention)
+    if (sizeof(T) != 2 || xq_gemm) {  // cross-attention query (else projected inside the cross-attention)
       rc::GemmArgs g{};
       g.A = A1; g.W = lw.xq_w; g.bias = lw.xq_b; g.M = R; g.N = C; g.K = C; g.lda = C; g.out = Q; g.ldo = C;
       RC_TRY(gemm<T>(c, RC_KC_GEMM_XQ, g, rc::EPI_STORE, gpart, gpf, s));
@@ -579,8 +589,9 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
         a.pmaps = pmaps;
       }
       RC_TRY(timed(c, RC_KC_ATTN_CROSS, s, [&] {
-        return sizeof(T) == 2 ? rc::launch_attention2q(a, B, max_rb, s)
-                              : rc::launch_attention<T>(a, B, max_rb, emit, s);
+        return sizeof(T) != 2 ? rc::launch_attention<T>(a, B, max_rb, emit, s)
+               : xq_gemm      ? rc::launch_attention2s(a, B, max_rb, s)
+                              : rc::launch_attention2q(a, B, max_rb, s);
       }));
       if (emit)
         RC_TRY(timed(c, RC_KC_MISC, s, [&] {

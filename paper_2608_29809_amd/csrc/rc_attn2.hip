@@ -372,6 +372,149 @@ __global__ __launch_bounds__(512, 1) void attn2q_kernel(AttnArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Cross-attention of projected queries (launch_attention2s), for rows enough
+// that the fused kernel above runs in several rounds: its projection re-reads
+// the head's weights for every 64 rows and runs at 300 TFLOP/s, which the
+// large-tile GEMM does at three times that rate, and this kernel is bound by
+// its queries' and outputs' bytes.
+//
+// One workgroup = 128 rows of one (chain, head), four waves of 32 rows with
+// all text keys: the scores of the (at most four) 32-key sub-tiles stay in
+// registers, one maximum, one pass of exponentials, one P.V chain (operand
+// layouts as above; V^T rows are n_keys wide, their 16-byte chunks swizzled by
+// the row).  37 KB of LDS: four workgroups per CU.
+// Measured, fused -> projection + this: 4096 rows 46 -> 29 us, 16384 rows
+// 170 -> 89 (this kernel 42.6: 1.8 TB/s of queries and outputs), 2458 rows
+// 35 -> 26, 1639 rows 23.4 -> 21.4.
+template <bool EMIT>
+__global__ __launch_bounds__(256) void attn2s_kernel(AttnArgs a) {
+  constexpr int D = kHeadDim, KB = 128 * D * 2;
+  constexpr int ONES_OFF = 2 * KB;
+  __shared__ __attribute__((aligned(1024))) char lds[ONES_OFF + 16];
+  char *ks = lds, *vs = lds + KB, *ones = lds + ONES_OFF;
+  if (threadIdx.x == 0) *(V16 *)ones = V16{{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u}};
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, r32 = lane & 31, C = a.hidden;
+  const int G = gridDim.x, Y = gridDim.y, T = G * Y * gridDim.z;
+  const int L = xcd_logical_id(blockIdx.x + G * (blockIdx.y + Y * blockIdx.z), T);
+  const int qt = L % G, h = (L / G) % Y, b = L / (G * Y);
+  const int2 rr = chain_rows(a, b);
+  const int r1 = rr.y, q0 = rr.x + qt * 128;
+  if (q0 >= r1) return;
+  const int nv = a.text_valid ? min(max(a.text_valid[b], 1), a.n_valid) : a.n_valid;
+  const char *Kg = (const char *)((const bf16 *)a.K + b * a.chain_stride + h * a.head_stride);
+  const bf16 *Vg = (const bf16 *)a.V + b * a.chain_stride + h * a.head_stride;  // transposed [72][n_keys]
+  const int my_q = q0 + wave * 32 + r32;
+  bf16x8 qf[5];
+  const bf16 *qrow = (const bf16 *)a.Q + (size_t)min(my_q, r1 - 1) * C + h * D;
+#pragma unroll
+  for (int c = 0; c < 5; ++c) {
+    const int d0 = c * 16 + g * 8;
+    qf[c] = Mfma<bf16>::zero();
+    if (d0 < D) qf[c] = *(const bf16x8 *)(qrow + d0);
+  }
+  // keys and values: n_keys * 9 chunks of 16 bytes each
+  const int cpr = a.n_keys / 8, n_copies = a.n_keys * 9 / 64;
+  for (int c = wave; c < n_copies; c += 4) {
+    const int ch = c * 64 + lane, d = ch / cpr;
+    lds_dma16(Kg + ch * 16, ks + c * 1024);
+    lds_dma16(Vg + (size_t)d * a.n_keys + (((ch & (cpr - 1)) ^ (d & (cpr - 1))) << 3), vs + c * 1024);
+  }
+  wait_vm0();
+  __syncthreads();
+
+  const float c2 = a.scale_log2;
+  const f32x16 zero16 = {};
+  f32x16 s[4];
+  float tmax = -INFINITY;
+#pragma unroll
+  for (int kt = 0; kt < 4; ++kt) {
+    if (kt * 32 < a.n_keys) {
+      const char *krow = ks + (kt * 32 + key_perm2(r32)) * (D * 2);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        bf16x8 kf = *(const bf16x8 *)(krow + (c < 4 || g == 0 ? (c * 16 + g * 8) * 2 : 0));
+        // (the upper half's dims 72..79 meet the zero query dims: any finite key values)
+        s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], c == 0 ? zero16 : s[kt], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int key = kt * 32 + (e >> 3) * 16 + g * 8 + (e & 7);
+      if (key >= nv) s[kt][e] = -INFINITY;
+      tmax = fmaxf(tmax, s[kt][e]);
+    }
+  }
+  tmax = half_swap_max(tmax);
+  const float mc = tmax == -INFINITY ? 0.0f : tmax * c2;
+  f32x16 o[3];
+#pragma unroll
+  for (int t = 0; t < 3; ++t) o[t] = zero16;
+  float sd[8];
+  if (EMIT) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int dl = j < a.n_delta ? a.delta[j] : -1;
+      sd[j] = 0.0f;
+      if (dl >= 0 && ((dl >> 3) & 1) == g) {
+        const int q = (dl >> 5) * 16 + ((dl >> 4) & 1) * 8 + (dl & 7);
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (kt * 16 + e == q) sd[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kt][e], c2, -mc));
+      }
+    }
+  }
+#pragma unroll
+  for (int kc = 0; kc < 8; ++kc) {  // 16 keys
+    if (kc * 16 < a.n_keys) {
+      bf16x8 pf;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) pf[k] = (bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(s[kc >> 1][(kc & 1) * 8 + k], c2, -mc));
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        const int d = min(t * 32 + r32, D - 1);
+        const char *va = vs + d * (a.n_keys * 2) + (((kc * 2 + g) ^ (d & (cpr - 1))) << 4);
+        if (t == 2 && r32 == 8) va = ones;
+        o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)va, pf, o[t], 0, 0, 0);
+      }
+    }
+  }
+  const float inv = 1.0f / __shfl(o[2][4], r32, 64);  // output row 72: the denominator
+  if (my_q >= r1) return;
+  if (EMIT) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j < a.n_delta && ((a.delta[j] >> 3) & 1) == g)
+        a.pmaps[((size_t)h * a.total_rows + my_q) * a.n_delta + j] = sd[j] * inv;
+  }
+  bf16 *orow = (bf16 *)a.O + (size_t)my_q * C + h * D;
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int d = t * 32 + i * 8 + g * 4;
+      if (d < D) {
+        bf16x4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = (bf16)(o[t][i * 4 + j] * inv);
+        *(bf16x4 *)(orow + d) = v;
+      }
+    }
+}
+
+hipError_t launch_attention2s(const AttnArgs &a, int n_chains, int max_rows, hipStream_t s) {
+  if (max_rows <= 0) return hipSuccess;
+  if ((a.n_keys != 64 && a.n_keys != 128) || a.splits != 1 || a.v_rowmajor || !a.Q || a.n_delta < 0 || a.n_delta > 8)
+    return hipErrorInvalidValue;
+  dim3 grid((max_rows + 127) / 128, a.hidden / kHeadDim, n_chains);
+  if (a.pmaps && a.n_delta > 0) rc_launch(attn2s_kernel<true>, grid, dim3(256), 0, s, a);
+  else rc_launch(attn2s_kernel<false>, grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_attention2q(const AttnArgs &a, int n_chains, int max_rows, hipStream_t s) {
   if (max_rows <= 0) return hipSuccess;
   if (a.n_keys % A2_BK != 0 || a.n_keys > 2 * A2_BK || a.splits != 1 || a.v_rowmajor || !a.q_x || !a.q_w ||

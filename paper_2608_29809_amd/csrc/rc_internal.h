@@ -178,6 +178,9 @@ template <typename T> hipError_t launch_attention(const AttnArgs &a, int n_chain
 // a.pmaps is set (rc_attn2.hip).  hidden 1152, at most 128 keys, one key
 // range.
 hipError_t launch_attention2q(const AttnArgs &a, int n_chains, int max_rows, hipStream_t s);
+// The same attention for queries a.Q that a GEMM has projected (unscaled); at
+// most 128 keys.
+hipError_t launch_attention2s(const AttnArgs &a, int n_chains, int max_rows, hipStream_t s);
 // bf16 self-attention (rc_attn4.hip); queries multiplied by log2(e)/sqrt(72).
 // The plan holds the 32-query halves per wave and the key splits, of at most
 // max_split_rows rows x splits in all.

@@ -87,6 +87,44 @@ def test_softmax_range(sign):
     _block(16, 16, [200, 3], seed=5, edit=edit)
 
 
+@pytest.mark.parametrize("text_len,valid", [(120, [120, 1, 57]), (64, [64, 33, 5]), (40, None)])
+def test_cross_attention_of_many_rows(text_len, valid):
+    """The cross-attention that takes projected queries (more than 256 tiles
+    of 64 rows and a head): chains of different length with padded prompts,
+    one or two text tiles, the maps of the first, last and padded columns."""
+    print("cross-attention", text_len, valid, flush=True)
+    s = synth.ModelShape(layers=1, text_dim=1152, text_len=text_len, grid_h=64, grid_w=32, dtype="bf16", token_mode=True)
+    W = synth.make_weights(s, seed=7, stress=True)
+    rng = np.random.default_rng(7)
+    counts = [1281, 1, 999]
+    idx = [np.sort(rng.choice(s.tokens, size=n, replace=False)).astype(np.int32) for n in counts]
+    slot = synth.make_cache_slot(s, 3, 7)
+    x = synth.bf16_round(rng.standard_normal((3, s.tokens, s.hidden)).astype(np.float32))
+    t_vec = rng.standard_normal(s.hidden).astype(np.float32)
+    text = synth.make_text(s, 3, 7)
+    delta = [0, 3, 4, 17, 31, 38, text_len - 1]
+    model = RegionCacheModel(s, W)
+    cache = model.alloc_cache(3, 1)
+    upload_slot(model, cache, 0, slot)
+    maps = torch.zeros((3, s.tokens, len(delta)), device="cuda")
+    model.reuse_step(cache, 0, ActiveSet.from_lists(idx), model.to_storage(x), 0, -1,
+                     model.prepare_text(model.to_storage(text)), delta, maps, t_vec=torch.from_numpy(t_vec).cuda(),
+                     text_valid=None if valid is None else torch.tensor(valid, dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    got = download_slot(cache, 0, 1, 3)
+    for b, n in enumerate(counts):
+        nv = text_len if valid is None else valid[b]
+        cols = [j for j in delta if j < nv]
+        X, K, V, H, m = O.reuse_block_tokens(s, W, x[b], idx[b], t_vec, text[b, :nv], slot["K"][0, b], slot["V"][0, b],
+                                             slot["H"][0, b], cols)
+        assert relerr(got["H"][0, b][idx[b]], np.asarray(H)[idx[b]]) < 2e-2, b
+        g = maps[b].cpu().numpy()[idx[b]]
+        m = np.asarray(m)
+        m = m[idx[b]] if m.shape[0] == s.tokens else m
+        assert relerr(g[:, [delta.index(j) for j in cols]], m) < 2e-2, b
+        assert not g[:, [i for i, j in enumerate(delta) if j >= nv]].any()  # padded tokens have probability 0
+
+
 @pytest.mark.parametrize("layers,batch", [(33, 1), (2, 3)])
 def test_text_of_all_blocks(layers, batch):
     """The text keys and values that one launch writes for up to 32 blocks:
