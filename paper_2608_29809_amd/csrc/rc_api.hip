@@ -116,7 +116,7 @@ constexpr int kMaxSplits = 8;
 int part_cap_rows(int max_rows) { return kMaxSplits * std::min(max_rows, 1024); }
 
 struct WsLayout {
-  size_t rows, offsets, X, A1, Q, O, G, part, ml, pmaps, e, th, temb, t0, gpart, fstats, fextra, fuv, total;
+  size_t rows, offsets, X, A1, Q, O, G, part, ml, pmaps, th, temb, t0, gpart, fstats, fextra, fuv, total;
   size_t gpart_floats;
   size_t txt_h, txt_y, txt_part, txt_part_floats, txt_total;
 };
@@ -137,7 +137,6 @@ WsLayout ws_layout(const rc_ctx *c, int max_rows, int B) {
   w.part = take(pr * c->C * 4);
   w.ml = take(pr * c->H * 2 * 4);
   w.pmaps = take((size_t)c->H * R * 8 * 4);
-  w.e = take(256 * 4);
   w.th = take((size_t)c->C * 4);
   w.temb = take((size_t)c->C * 4);
   w.t0 = take((size_t)6 * c->C * 4);
@@ -389,7 +388,7 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
   float *X = (float *)(wsb + wl.X);
   void *A1 = wsb + wl.A1, *Q = wsb + wl.Q, *O = wsb + wl.O, *G = wsb + wl.G;
   float *part = (float *)(wsb + wl.part), *ml = (float *)(wsb + wl.ml), *pmaps = (float *)(wsb + wl.pmaps);
-  float *e = (float *)(wsb + wl.e), *th = (float *)(wsb + wl.th), *temb = (float *)(wsb + wl.temb);
+  float *th = (float *)(wsb + wl.th), *temb = (float *)(wsb + wl.temb);
   float *t0 = (float *)(wsb + wl.t0);
   float *gpart = (float *)(wsb + wl.gpart);
   const size_t gpf = wl.gpart_floats;
@@ -412,11 +411,6 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
     fold_uv = fold_nt && p1.big;
   }
 
-  if (dense) RC_TRY(timed(c, RC_KC_MISC, s, [&] { return rc::launch_dense_offsets((int *)offsets_dev, B, N, s); }));
-  RC_TRY(timed(c, RC_KC_MISC, s, [&] {
-    return rc::launch_build_rows(offsets_dev, dense ? nullptr : act->idx, B, R, rows, s);
-  }));
-
   // conditioning (adaLN-single)
   const rc_weights &W = c->w;
   if (c->cfg.token_mode) {
@@ -424,8 +418,9 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
       return rc::launch_gemv<T>(W.tblock_w, W.tblock_b, io->t_vec, 6 * C, C, 1, 0, t0, s);
     }));
   } else {
-    RC_TRY(timed(c, RC_KC_COND, s, [&] { return rc::launch_timestep_features((float)io->timestep, e, s); }));
-    RC_TRY(timed(c, RC_KC_COND, s, [&] { return rc::launch_gemv<T>(W.temb_w1, W.temb_b1, e, C, 256, 0, 1, th, s); }));
+    RC_TRY(timed(c, RC_KC_COND, s, [&] {
+      return rc::launch_timestep_gemv<T>(W.temb_w1, W.temb_b1, (float)io->timestep, C, th, s);
+    }));
     RC_TRY(timed(c, RC_KC_COND, s, [&] { return rc::launch_gemv<T>(W.temb_w2, W.temb_b2, th, C, C, 0, 0, temb, s); }));
     RC_TRY(timed(c, RC_KC_COND, s, [&] {
       return rc::launch_gemv<T>(W.tblock_w, W.tblock_b, temb, 6 * C, C, 1, 0, t0, s);
@@ -448,6 +443,10 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
   {
     rc::EmbedArgs ea{};
     ea.rows = rows;
+    ea.offsets = offsets_dev;
+    ea.idx = dense ? nullptr : act->idx;
+    ea.dense_offsets = dense ? (int *)offsets_dev : nullptr;
+    ea.B = B;
     ea.X = X;
     ea.C = C;
     ea.N = N;

@@ -413,7 +413,7 @@ __global__ __launch_bounds__(256, 2) void attn4_kernel(AttnArgs a) {
 // Combine of normalised bf16 split outputs: O = sum_s w_s O_s / sum_s w_s with
 // w_s = 2^(m_s - max m) l_s, in split order.  One thread per (row, head,
 // 8 dims); all loads are issued before use.
-__global__ __launch_bounds__(256) void attn_combine_norm_kernel(const bf16 *Opart, const float *ML, bf16 *O, int R,
+__global__ __launch_bounds__(64) void attn_combine_norm_kernel(const bf16 *Opart, const float *ML, bf16 *O, int R,
                                                                 int heads, int splits) {
   constexpr int G = kHeadDim / 8;
   const int C = heads * kHeadDim;
@@ -456,7 +456,7 @@ hipError_t launch_attn_combine_norm(const void *Opart, const float *ML, void *O,
   if (R <= 0) return hipSuccess;
   if (splits < 1 || splits > 16) return hipErrorInvalidValue;
   const long n = (long)R * heads * (kHeadDim / 8);
-  rc_launch(attn_combine_norm_kernel, dim3((n + 255) / 256), dim3(256), 0, s, (const bf16 *)Opart, ML, (bf16 *)O, R,
+  rc_launch(attn_combine_norm_kernel, dim3((n + 63) / 64), dim3(64), 0, s, (const bf16 *)Opart, ML, (bf16 *)O, R,
             heads, splits);
   return hipGetLastError();
 }

@@ -12,7 +12,11 @@ struct MapsDelta {
 };
 
 struct EmbedArgs {
-  const int *rows;        // packed (chain<<16)|token
+  int *rows;              // [R] out: packed (chain<<16)|token
+  const int *offsets;     // [B+1] device row offsets (read if idx is given)
+  const int *idx;         // [R] tokens, or null: the dense set
+  int *dense_offsets;     // [B+1] out: b N (dense set only)
+  int B;
   float *X;               // [R][C] residual stream
   int C, N, gh, gw;
   const float *latent;    // [B][4][2gh][2gw] (patch mode)
@@ -40,16 +44,16 @@ struct FinalArgs {
   float gscale;
 };
 
-hipError_t launch_build_rows(const int *offsets, const int *idx, int B, int R, int *rows, hipStream_t s);
-hipError_t launch_dense_offsets(int *offsets, int B, int N, hipStream_t s);
 template <typename T> hipError_t launch_embed(const EmbedArgs &a, int R, hipStream_t s);
 template <typename T>
 hipError_t launch_ln_mod(const float *X, int R, int C, const float *table, const float *t0, int shift_row,
                          float eps, void *out, hipStream_t s);
-hipError_t launch_timestep_features(float t, float *e, hipStream_t s);
 template <typename T>
 hipError_t launch_gemv(const void *W, const float *bias, const float *x, int N, int K, int silu_in, int silu_out,
                        float *y, hipStream_t s);
+// The first timestep product: 256 features of t, silu on the output.
+template <typename T>
+hipError_t launch_timestep_gemv(const void *W, const float *bias, float t, int N, float *y, hipStream_t s);
 template <typename T> hipError_t launch_final_ddim(const FinalArgs &a, hipStream_t s);
 // Copy of the key, value and hidden-state rows of `rows` (packed chain/token)
 // from a staging slot to a cache slot of the same layout (bf16 only; the

@@ -8,41 +8,27 @@
 
 namespace rc {
 
-// rows[r] = (chain << 16) | token for r in [0, R); idx == null means the
-// dense identity set (token = r - offsets[chain]).
-__global__ void build_rows_kernel(const int *offsets, const int *idx, int B, int R, int *rows) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= R) return;
-  int b = 0;
-  while (b + 1 < B && offsets[b + 1] <= r) ++b;
-  const int tok = idx ? idx[r] : r - offsets[b];
-  rows[r] = (b << 16) | tok;
-}
-
-hipError_t launch_build_rows(const int *offsets, const int *idx, int B, int R, int *rows, hipStream_t s) {
-  if (R <= 0) return hipSuccess;
-  rc_launch(build_rows_kernel, dim3((R + 255) / 256), dim3(256), 0, s, offsets, idx, B, R, rows);
-  return hipGetLastError();
-}
-
-// Dense-step offsets: offsets[b] = b*N for b = 0..B (B+1 entries, any B).
-__global__ void dense_offsets_kernel(int *offsets, int B, int N) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b <= B) offsets[b] = b * N;
-}
-
-hipError_t launch_dense_offsets(int *offsets, int B, int N, hipStream_t s) {
-  rc_launch(dense_offsets_kernel, dim3((B + 1 + 255) / 256), dim3(256), 0, s, offsets, B, N);
-  return hipGetLastError();
-}
-
 // X[r][:] = patch(token) . W_pe^T + b_pe + pos(token), or in token mode the
-// gathered hidden row.  One workgroup per row.
+// gathered hidden row.  One workgroup per row, which also writes the row's
+// packed number rows[r] = (chain << 16) | token (idx == null: the dense set,
+// whose offsets b N it writes too); as launches of their own these took 4.5 us
+// each.
 template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
   const int r = blockIdx.x;
-  const int pk = a.rows[r];
-  const int b = row_chain(pk), tok = row_token(pk);
+  int b = 0, tok;
+  if (a.idx) {
+    while (b + 1 < a.B && a.offsets[b + 1] <= r) ++b;
+    tok = a.idx[r];
+  } else {
+    b = r / a.N;
+    tok = r - b * a.N;
+    if (threadIdx.x == 0) {
+      if (tok == 0) a.dense_offsets[b] = r;
+      if (r == a.B * a.N - 1) a.dense_offsets[a.B] = r + 1;
+    }
+  }
+  if (threadIdx.x == 0) a.rows[r] = (b << 16) | tok;
   float *xrow = a.X + (size_t)r * a.C;
   if (a.tokens_in) {
     const T *src = (const T *)a.tokens_in + ((size_t)b * a.N + tok) * a.C;
@@ -155,21 +141,6 @@ hipError_t launch_ln_mod(const float *X, int R, int C, const float *table, const
 template hipError_t launch_ln_mod<bf16>(const float *, int, int, const float *, const float *, int, float, void *, hipStream_t);
 template hipError_t launch_ln_mod<float>(const float *, int, int, const float *, const float *, int, float, void *, hipStream_t);
 
-// Timestep features e(t) = [cos(t f_k), sin(t f_k)], f_k = 10000^(-k/128).
-__global__ void timestep_features_kernel(float t, float *e) {
-  const int k = threadIdx.x;
-  if (k >= 128) return;
-  const float f = exp2f(-(float)k / 128.0f * 13.287712379549449f);
-  const float arg = t * f;
-  e[k] = cosf(arg);
-  e[128 + k] = sinf(arg);
-}
-
-hipError_t launch_timestep_features(float t, float *e, hipStream_t s) {
-  rc_launch(timestep_features_kernel, dim3(1), dim3(128), 0, s, t, e);
-  return hipGetLastError();
-}
-
 // y[n] = act_out( W[n] . act_in(x) + b[n] ), one wave per output.
 // 8 consecutive inputs of one row as floats (16-byte loads).
 template <typename T> __device__ __forceinline__ void load8(const T *p, float *v);
@@ -189,9 +160,20 @@ template <> __device__ __forceinline__ void load8<bf16>(const bf16 *p, float *v)
 
 // y[n] = act(W[n] . act_in(x) + b[n]); one wave per output, each lane takes
 // 8 consecutive inputs per pass (K % 8 == 0, K <= 1536), every load first.
-template <typename T>
-__global__ __launch_bounds__(256) void gemv_kernel(const T *W, const float *bias, const float *x, int N, int K,
+// FEAT: x is the timestep features [cos(t f_k), sin(t f_k)], f_k =
+// 10000^(-k/128), k < 128 (K = 256), computed by every workgroup (one sine or
+// cosine per thread; a launch of their own took 4 us).
+template <typename T, bool FEAT>
+__global__ __launch_bounds__(256) void gemv_kernel(const T *W, const float *bias, const float *x, float t, int N, int K,
                                                    int silu_in, int silu_out, float *y) {
+  __shared__ __attribute__((aligned(16))) float feat[FEAT ? 256 : 4];
+  if (FEAT) {
+    const int k = threadIdx.x & 127;
+    const float arg = t * exp2f(-(float)k / 128.0f * 13.287712379549449f);
+    feat[threadIdx.x] = threadIdx.x < 128 ? cosf(arg) : sinf(arg);
+    __syncthreads();
+    x = feat;
+  }
   const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (n >= N) return;
@@ -225,12 +207,21 @@ template <typename T>
 hipError_t launch_gemv(const void *W, const float *bias, const float *x, int N, int K, int silu_in, int silu_out,
                        float *y, hipStream_t s) {
   if (K % 8 || K > 64 * 8 * 3) return hipErrorInvalidValue;
-  rc_launch(gemv_kernel<T>, dim3((N + 3) / 4), dim3(256), 0, s, (const T *)W, bias, x, N, K, silu_in,
+  rc_launch(gemv_kernel<T, false>, dim3((N + 3) / 4), dim3(256), 0, s, (const T *)W, bias, x, 0.0f, N, K, silu_in,
                      silu_out, y);
   return hipGetLastError();
 }
 template hipError_t launch_gemv<bf16>(const void *, const float *, const float *, int, int, int, int, float *, hipStream_t);
 template hipError_t launch_gemv<float>(const void *, const float *, const float *, int, int, int, int, float *, hipStream_t);
+
+template <typename T>
+hipError_t launch_timestep_gemv(const void *W, const float *bias, float t, int N, float *y, hipStream_t s) {
+  rc_launch(gemv_kernel<T, true>, dim3((N + 3) / 4), dim3(256), 0, s, (const T *)W, bias, (const float *)nullptr, t, N,
+            256, 0, 1, y);
+  return hipGetLastError();
+}
+template hipError_t launch_timestep_gemv<bf16>(const void *, const float *, float, int, float *, hipStream_t);
+template hipError_t launch_timestep_gemv<float>(const void *, const float *, float, int, float *, hipStream_t);
 
 // Final layer + DDIM for each computed row: eps = (LN(X)(1+sc)+sh) W_f^T + b_f
 // for the noise channels of the 2x2 patch, then x' = ca * x + cb * eps written
