@@ -654,7 +654,7 @@ def class_work(shape, R, B):
 KERNEL_SOURCES = {  # sources whose text fixes a kernel class's code
     "attn_self": ["rc_attn4.hip", "rc_common.h", "rc_internal.h", "rc_launch.h"],
     "attn_cross": ["rc_attn2.hip", "rc_common.h", "rc_internal.h", "rc_launch.h"],
-    "gemm": ["rc_gemm2.hip", "rc_common.h", "rc_internal.h", "rc_launch.h"],
+    "gemm": ["rc_gemm2.hip", "rc_gemm3.hip", "rc_common.h", "rc_internal.h", "rc_launch.h"],
 }
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "hbm_traffic_reuse_step_1024px.md")
 
