@@ -22,12 +22,14 @@
 // v_exp_f32 of the accumulator, relative to the fixed reference 0: bf16
 // probabilities and fp32 sums keep their relative precision over the whole
 // exponent range, so any reference serves as long as nothing leaves the
-// range.  A workgroup one of whose denominators is not inside [2^-80, 2^80]
-// (or is NaN) starts again relative to each query's maximum over the key
-// range: a pass over the keys finds it, and its negative goes as three bf16
-// parts (24 bits: exactly) into the query dims 72..74, which meet ones in
-// the padded key dims.  Probabilities below 2^-126 are lost, at most 2^-32
-// of an accepted denominator for 16384 keys.
+// range.  A workgroup one of whose denominators is not inside [2^-40, 2^80]
+// (or is NaN), or one of whose sums of values is not finite (values above
+// 2^48 beside a large denominator), starts again relative to each query's
+// maximum over the key range: a pass over the keys finds it, and its negative
+// goes as three bf16 parts (24 bits: exactly) into the query dims 72..74,
+// which meet ones in the padded key dims.  Probabilities below 2^-126 are
+// lost, at most 2^-72 of an accepted denominator for 16384 keys, and values
+// above 2^-86 keep their precision.
 //
 // A wave holds QH = 2 or 1 halves of 32 queries.  What bounds the kernel: for
 // many queries the matrix core at the clock that the power limit leaves (63 %
@@ -224,8 +226,9 @@ __global__ __launch_bounds__(256, 2) void attn4_kernel(AttnArgs a) {
   f32x16 o[QH][2];  // dims 0..63
   f32x4 o2[QH][2];  // dims 64..71, the denominator (row 72) and seven unused rows, queries 0..15 and 16..31
   // Softmax reference: 0 at first.  A workgroup whose denominators leave
-  // [2^-80, 2^80] takes its maxima over all its keys as the references
-  // (exactly: three bf16 parts in the padded query dims) and starts again.
+  // [2^-40, 2^80], or whose sums overflow, takes its maxima over all its keys
+  // as the references (exactly: three bf16 parts in the padded query dims) and
+  // starts again.
   float m_ref[QH];
 #pragma unroll
   for (int hh = 0; hh < QH; ++hh) m_ref[hh] = 0.0f;
@@ -364,11 +367,18 @@ __global__ __launch_bounds__(256, 2) void attn4_kernel(AttnArgs a) {
     }
     if (again) break;
     bool bad = false;
+    float nan0 = 0.0f;  // 0, or NaN if a sum is not finite
 #pragma unroll
     for (int hh = 0; hh < QH; ++hh)
 #pragma unroll
-      for (int q = 0; q < 2; ++q) bad = bad || (tw == 2 && !(o2[hh][q][0] < 0x1p80f && o2[hh][q][0] > 0x1p-80f));
-    if (__any(bad) && lane == 0) *flag = 1;
+      for (int q = 0; q < 2; ++q) {
+        bad = bad || (tw == 2 && !(o2[hh][q][0] < 0x1p80f && o2[hh][q][0] > 0x1p-40f));
+#pragma unroll
+        for (int e = 0; e < 16; ++e) nan0 = __builtin_fmaf(o[hh][q][e], 0.0f, nan0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) nan0 = __builtin_fmaf(o2[hh][q][e], 0.0f, nan0);
+      }
+    if (__any(bad || nan0 != 0.0f) && lane == 0) *flag = 1;
     __syncthreads();
     if (!*flag) break;
     again = true;
@@ -403,9 +413,11 @@ __global__ __launch_bounds__(256, 2) void attn4_kernel(AttnArgs a) {
     }
     if (my_q >= r1) continue;
     if (a.splits > 1 && g == 0) {
+      // (relative to 0 the denominator's power of two goes into the reference,
+      // so that the combine's weights, like the probabilities, stay near 1)
       float *ml = a.ML + (((size_t)split * a.total_rows + my_q) * heads + h) * 2;
-      ml[0] = m_ref[hh];
-      ml[1] = l_tot;
+      ml[0] = again ? m_ref[hh] : (float)__builtin_amdgcn_frexp_expf(l_tot);
+      ml[1] = again ? l_tot : __builtin_amdgcn_frexp_mantf(l_tot);
     }
   }
 }

@@ -88,7 +88,7 @@ struct AttnArgs {
   int splits;            // key-range splits (grid.y = heads*splits)
   void *O;               // [R][C] E output (splits == 1)
   float *Opart;          // [splits][R][C] split outputs (splits > 1): fp32 unnormalised (fp32 path) or bf16 normalised (launch_attention4)
-  float *ML;             // [splits][R][heads][2] running max (log2 domain) and sum
+  float *ML;             // [splits][R][heads][2] softmax reference (log2 domain) and denominator relative to it
   int total_rows;        // R (stride of the partial arrays)
   // map emission (cross-attention)
   int n_delta;

@@ -2,6 +2,7 @@
 path through the C ABI, run the oracle on the same inputs, compare."""
 from __future__ import annotations
 
+import ctypes as C
 import functools
 
 import numpy as np
@@ -131,3 +132,51 @@ def teacher_forced_dense(shape, W, latent_b, t, tkv_o, got_b):
         out.append(_block_errors(gH, X, X_in, got_b["K"][l], K, got_b["V"][l], V, u if l > 0 else u / 2))
         X_in = gH
     return out
+
+
+def run_block(shape, W, idx, slot, x, t_vec, text, text_kv=None):
+    """One token-mode reuse step over `slot` through the block call; returns
+    the slot it leaves.  text_kv: a function that may change the prepared text
+    keys and values before the step."""
+    from paper_2608_29809_amd.runtime import ActiveSet, RegionCacheModel
+    model = RegionCacheModel(shape, W)
+    B = len(idx)
+    cache = model.alloc_cache(B, 1)
+    upload_slot(model, cache, 0, slot)
+    tkv = model.prepare_text(model.to_storage(text))
+    if text_kv:
+        text_kv(tkv.view(model.dtype))
+    model.reuse_step(cache, 0, ActiveSet.from_lists(idx), model.to_storage(x), 0, -1, tkv,
+                     t_vec=torch.from_numpy(t_vec).cuda())
+    torch.cuda.synchronize()
+    return download_slot(cache, 0, shape.layers, B)
+
+
+class _GemmPlan(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("bm", "bn", "splits", "kg", "stages", "wgm", "wgn")] + [("big", C.c_bool)]
+
+
+class _AttnPlan(C.Structure):
+    _fields_ = [("qh", C.c_int), ("splits", C.c_int)]
+
+
+EPI = dict(store=0, gelu=1, resid=2, qkv=3)
+
+
+def gemm_plan(M, N, K, epi, partial_floats=None):
+    """(large tiles?, tile rows, tile columns, splits, whole plan) of a bf16
+    GEMM of the step; partial_floats defaults to the step's split workspace."""
+    from paper_2608_29809_amd import abi
+    f = abi.LIB._ZN2rc9plan_gemmEiiimi
+    f.restype, f.argtypes = _GemmPlan, [C.c_int] * 3 + [C.c_size_t, C.c_int]
+    p = f(M, N, K, min(M, 2048) * 8 * 1152 if partial_floats is None else partial_floats, EPI[epi])
+    return p.big, p.bm, p.bn, p.splits, tuple(getattr(p, n) for n, _ in p._fields_)
+
+
+def attention_plan(counts, tokens, heads=16):
+    """(32-query halves per wave, key splits) of a step's bf16 self-attention."""
+    from paper_2608_29809_amd import abi
+    f = abi.LIB._ZN2rc14plan_attentionEPKiiiil
+    f.restype, f.argtypes = _AttnPlan, [C.POINTER(C.c_int), C.c_int, C.c_int, C.c_int, C.c_long]
+    p = f((C.c_int * len(counts))(*counts), len(counts), heads, tokens, 8 * min(sum(counts), 1024))
+    return p.qh, p.splits
