@@ -69,6 +69,8 @@ __device__ __forceinline__ int key_perm4(int m) {
 // copies first (wait_tiles), and reads of a ring slot are consumed before the
 // barrier that frees it.
 __device__ __forceinline__ void lds_barrier4() { asm volatile("s_barrier" ::: "memory"); }
+// The first barrier: the constants that thread 0 wrote to LDS are there too.
+__device__ __forceinline__ void lds_barrier4_first() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 template <int N> __device__ __forceinline__ void wait_vm4() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(256, 2) void attn4_kernel(AttnArgs a) {
   if (QH == 1) {
     start_ring();
     wait_tiles(min(n - 1, STAGES - 2));
-    lds_barrier4();
+    lds_barrier4_first();
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       const int d0 = c * 16 + g * 8;
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(256, 2) void attn4_kernel(AttnArgs a) {
       for (int c = 0; c < 5; ++c) asm volatile("" : "+v"(qf[hh][c]));
     wait_vm4<0>();
     if (n > 1) issue(1, 1);
-    lds_barrier4();
+    lds_barrier4_first();
   }
 
   const int k_off = key_perm4(r32) * (D * 2) + g * 16;
