@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
   constexpr int IT = GF_BM * BN / 4 / 256;
   const int col = (tid % (BN / 4)) * 4, n = n0 + col, row0 = tid / (BN / 4);
   constexpr int RSTEP = 1024 / BN;
-  f32x4 bb = f32x4{0.0f, 0.0f, 0.0f, 0.0f}, gt = bb + 1.0f;
+  f32x4 bb = f32x4{0.0f, 0.0f, 0.0f, 0.0f}, gt = f32x4{1.0f, 1.0f, 1.0f, 1.0f};
   if (g.bias) bb = *(const f32x4 *)(g.bias + n);
   if (EPI == EPI_RESID && g.gate) gt = *(const f32x4 *)(g.gate + n);
   if (EPI == EPI_RESID && g.gate && g.gate2) gt += *(const f32x4 *)(g.gate2 + n);
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
   for (int it = 0; it < IT; ++it) {
     const int row = row0 + it * RSTEP, m = m0 + row;
     if (m >= g.M) continue;
-    f32x4 v = bb * 0.0f;
+    f32x4 v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int w = 0; w < 4; ++w) v += *(const f32x4 *)((const float *)lds + (w * GF_BM + row) * CLD + col);
     v += bb;
