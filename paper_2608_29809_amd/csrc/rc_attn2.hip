@@ -391,9 +391,12 @@ template <bool EMIT>
 __global__ __launch_bounds__(256) void attn2s_kernel(AttnArgs a) {
   constexpr int D = kHeadDim, KB = 128 * D * 2;
   constexpr int ONES_OFF = 2 * KB;
-  __shared__ __attribute__((aligned(1024))) char lds[ONES_OFF + 16];
-  char *ks = lds, *vs = lds + KB, *ones = lds + ONES_OFF;
-  if (threadIdx.x == 0) *(V16 *)ones = V16{{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u}};
+  __shared__ __attribute__((aligned(1024))) char lds[ONES_OFF + 32];
+  char *ks = lds, *vs = lds + KB, *ones = lds + ONES_OFF, *zeros = ones + 16;
+  if (threadIdx.x == 0) {
+    *(V16 *)ones = V16{{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u}};
+    *(V16 *)zeros = V16{{0u, 0u, 0u, 0u}};
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, r32 = lane & 31, C = a.hidden;
   const int G = gridDim.x, Y = gridDim.y, T = G * Y * gridDim.z;
@@ -434,8 +437,8 @@ __global__ __launch_bounds__(256) void attn2s_kernel(AttnArgs a) {
       const char *krow = ks + (kt * 32 + key_perm2(r32)) * (D * 2);
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
-        bf16x8 kf = *(const bf16x8 *)(krow + (c < 4 || g == 0 ? (c * 16 + g * 8) * 2 : 0));
-        // (the upper half's dims 72..79 meet the zero query dims: any finite key values)
+        // (dims 72..79, the upper half's last: zeros, as a key may be infinite)
+        const bf16x8 kf = *(const bf16x8 *)(c < 4 || g == 0 ? krow + (c * 16 + g * 8) * 2 : zeros);
         s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], c == 0 ? zero16 : s[kt], 0, 0, 0);
       }
     }

@@ -38,3 +38,25 @@ def test_infinite_bias(dtype):
     assert (got[:, 7] == np.inf).all() and (got[:, 640] == -np.inf).all()
     rest = np.setdiff1d(np.arange(C), [7, 640])
     assert np.array_equal(got[:, rest], ref[:, rest])
+
+
+@pytest.mark.parametrize("rows", [100, 2000])
+@pytest.mark.parametrize("dim", [3, 70])
+def test_infinite_text_key(rows, dim):
+    """A text key of minus infinity in one dimension, where every query is
+    positive, has probability 0: the same result as with a key of -1e30.
+    Both forms of the cross-attention, a dimension of its first and of its
+    last operand."""
+    print("infinite text key", rows, dim, flush=True)
+    idx = [np.sort(np.random.default_rng(1).choice(2048, rows, replace=False)).astype(np.int32)]
+
+    def edit(lw):  # queries of 50 plus their usual few units in that dimension of every head
+        lw["xq_b"][dim::72] = 50.0
+
+    out = []
+    for value in (-1e30, -float("inf")):
+        def text_kv(kv):  # keys [layer, chain][head][128][72], then the values
+            kv.view(2, 16, 128, 72)[0, :, 5, dim] = value
+        out.append(_block("bf16", 32, 64, idx, edit, text_kv)["H"][0, 0][idx[0]])
+    assert np.isfinite(out[0]).all()
+    assert np.array_equal(out[0], out[1])
