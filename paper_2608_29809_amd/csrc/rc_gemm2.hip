@@ -836,7 +836,10 @@ GemmPlan plan_gemm(int M, int N, int K, size_t partial_cap_floats, int epi) {
       if (kind == 1 && sp == 1) ends = std::max(ends, mn * 10.0 / 5.5e6);
       double us = (t.slots > 256 ? 9.0 : 3.0) + rounds * nst * t.stage + ends;
       us += sp > 1 ? 4.0 + mn * 4.0 * (sp + 2) / 4e6 : norm;
-      if (us < best) {
+      // (the later of equal estimates, which rounding would alternate from row to
+      // row: MLP-down at 4801 to 4864 rows, four blocks of 2048 px 3.07 ms with
+      // the large tiles, 3.09 without)
+      if (us < 1.0001 * best) {
         best = us;
         p = GemmPlan{t.bm, t.bn, sp, t.kg, 0, 0, 0, true};
       }
