@@ -281,7 +281,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG, 2) void gemm3_kernel(GemmArgs 
           cg[k] = f32x4{1.0f, 1.0f, 1.0f, 1.0f};
           if (NCOL && g.bias) cb[k] = col(0, k);
           if (RESID && g.gate) cg[k] = g.gate2 ? col(1, k) + col(2, k) : col(1, k);
-          if (RESID) cs[k] = g.fold_stats ? 1.0f + col(3, k) + col(4, k) : cg[k] * 0.0f + 1.0f;
+          if (RESID) cs[k] = g.fold_stats ? 1.0f + col(3, k) + col(4, k) : f32x4{1.0f, 1.0f, 1.0f, 1.0f};
           if (FOLD) {
             cg[k] = -col(1, k);
             cb[k] += col(2, k);
