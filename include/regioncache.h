@@ -190,6 +190,9 @@ rc_status rc_cache_latent_offset(const rc_ctx *ctx, const rc_cache_view *cache, 
 
 /* Per-turn text preparation: caption projection (skipped in token mode) and,
  * for every block, the cross-attention keys and values of the text tokens.
+ * The workspace holds at least two [batch][text_len][hidden] arrays of E, each
+ * rounded up to 256 bytes; with rc_workspace_bytes(ctx, any, batch) the caption
+ * projection is also split over more workgroups.
  * txt: device E [batch][text_len][text_dim].  text_kv: device E buffer of
  * rc_text_kv_bytes(ctx, batch); entry (l, b) holds K [H][Mp][72] then V
  * transposed [H][72][Mp], Mp = text_len rounded up to 64, padding zero. */

@@ -151,7 +151,8 @@ WsLayout ws_layout(const rc_ctx *c, int max_rows, int B) {
   auto take2 = [&](size_t bytes) { size_t at = t; t = align256(t + bytes); return at; };
   w.txt_h = take2((size_t)B * c->M * c->C * c->esz);
   w.txt_y = take2((size_t)B * c->M * c->C * c->esz);
-  // split partials of the caption projection's first product (bf16)
+  // split partials of the caption projection's first product (bf16); less
+  // room than this leaves it unsplit
   w.txt_part_floats = c->esz == 2 && !c->cfg.token_mode ? (size_t)4 * B * c->M * c->C : 0;
   w.txt_part = take2(w.txt_part_floats * 4);
   w.txt_total = t;
@@ -681,8 +682,9 @@ rc_status run_text(rc_ctx *c, const void *txt, int B, void *text_kv, void *ws, s
   const WsLayout wl = ws_layout(c, 1, B);
   RC_CHECK(ws, RC_ERR_INVALID_ARG, "workspace is null");
   RC_CHECK(aligned16(ws), RC_ERR_ALIGN, "workspace not 16-byte aligned");
-  RC_CHECK(ws_bytes >= wl.txt_total, RC_ERR_CAPACITY, "workspace has %zu bytes, text preparation needs %zu",
-           ws_bytes, wl.txt_total);
+  RC_CHECK(ws_bytes >= wl.txt_part, RC_ERR_CAPACITY, "workspace has %zu bytes, text preparation needs %zu",
+           ws_bytes, wl.txt_part);
+  const size_t part_floats = std::min(wl.txt_part_floats, (ws_bytes - wl.txt_part) / sizeof(float));
   char *wsb = (char *)ws;
   const size_t kv_bytes = (size_t)c->L * B * text_kv_elems_per_entry(c) * c->esz;
   RC_TRY(timed(c, RC_KC_MISC, s, [&] { return rc::launch_zero(text_kv, kv_bytes, s); }));
@@ -691,7 +693,7 @@ rc_status run_text(rc_ctx *c, const void *txt, int B, void *text_kv, void *ws, s
     rc::GemmArgs g{};
     g.A = txt; g.W = c->w.cap_w1; g.bias = c->w.cap_b1; g.M = B * M; g.N = C; g.K = c->cfg.text_dim;
     g.lda = c->cfg.text_dim; g.out = wsb + wl.txt_h; g.ldo = C;
-    RC_TRY(gemm<T>(c, RC_KC_GEMM, g, rc::EPI_GELU, (float *)(wsb + wl.txt_part), wl.txt_part_floats, s));
+    RC_TRY(gemm<T>(c, RC_KC_GEMM, g, rc::EPI_GELU, (float *)(wsb + wl.txt_part), part_floats, s));
     rc::GemmArgs g2{};
     g2.A = wsb + wl.txt_h; g2.W = c->w.cap_w2; g2.bias = c->w.cap_b2; g2.M = B * M; g2.N = C; g2.K = C;
     g2.lda = C; g2.out = wsb + wl.txt_y; g2.ldo = C;
