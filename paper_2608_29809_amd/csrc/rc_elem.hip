@@ -18,7 +18,14 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
   const int r = blockIdx.x;
   int b = 0, tok;
   if (a.idx) {
-    while (b + 1 < a.B && a.offsets[b + 1] <= r) ++b;
+    // the chain with offsets[b] <= r < offsets[b + 1] by bisection: every
+    // workgroup searches (in order of chains the kernel took 28 us for 300
+    // chains of four rows, 2.6 ms for 4096, 39 ms for 16384)
+    for (int hi = a.B - 1; b < hi;) {
+      const int mid = (b + hi) >> 1;
+      if (a.offsets[mid + 1] <= r) b = mid + 1;
+      else hi = mid;
+    }
     tok = a.idx[r];
   } else {
     b = r / a.N;

@@ -57,6 +57,15 @@ def test_edges(gh, gw, counts):
     _block(gh, gw, counts, seed=gh + gw)
 
 
+@pytest.mark.parametrize("counts", [[0, 0, 5], [7, 0, 0], [0] * 9 + [1, 0, 64, 0, 2] + [0] * 7, [1] * 16 + [3],
+                                    [(5 * b) % 9 for b in range(70)]])
+def test_many_chains(counts):
+    """Rows found in their chains: empty chains first, last and in between,
+    more chains than the kernel arguments hold offsets of (16)."""
+    print("chains", counts, flush=True)
+    _block(8, 8, counts, seed=len(counts))
+
+
 @pytest.mark.parametrize("rows", [1009, 2449, 3969])
 def test_large_gemm_tiles(rows):
     """Row counts that take the large GEMM tiles, each with a last row tile of
