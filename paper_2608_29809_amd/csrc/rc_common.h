@@ -138,15 +138,22 @@ __device__ __forceinline__ void lds_dma16(const void *gsrc, const void *lds_wave
 }
 
 // The same copy with a wave-uniform base address and a 32-bit byte offset per
-// lane: one address register per lane however many bases are in use.
-__device__ __forceinline__ void lds_dma16s(const void *base, unsigned lane_off, const void *lds_wave_base) {
-  const unsigned dst = __builtin_amdgcn_readfirstlane(
-      (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char *)lds_wave_base);
+// lane: one address register per lane however many bases are in use.  The
+// destination as an LDS address (lds_address, once per array) or as a pointer,
+// whose conversion is five scalar instructions each time.
+__device__ __forceinline__ unsigned lds_address(const void *lds) {
+  return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char *)lds;
+}
+__device__ __forceinline__ void lds_dma16s(const void *base, unsigned lane_off, unsigned lds_wave_base) {
+  const unsigned dst = __builtin_amdgcn_readfirstlane(lds_wave_base);
   const uint64_t u = (uint64_t)(uintptr_t)base;  // (the scalar operand, also where the compiler kept it in vectors)
   const uint64_t src = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32 |
                        (unsigned)__builtin_amdgcn_readfirstlane((int)u);
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(lane_off), "s"(dst), "s"(src)
                : "memory", "m0");
+}
+__device__ __forceinline__ void lds_dma16s(const void *base, unsigned lane_off, const void *lds_wave_base) {
+  lds_dma16s(base, lane_off, lds_address(lds_wave_base));
 }
 
 // Memory-side cache warm-up of a buffer a later kernel reads: one dword of
