@@ -76,6 +76,7 @@ struct rc_ctx {
   std::vector<rc_layer_weights> layers;
   int N, C, H, F, L, M, Mp;
   size_t esz;
+  bool vec16;  // every bias and modulation table is 16-byte aligned (not checked by rc_create)
   // per-kernel timing
   bool timing = false;
   struct Rec { int cls; hipEvent_t a, b; };
@@ -263,14 +264,21 @@ double alpha_bar(int t) {
 
 // ------------------------------------------------------------------ the step
 
-// One GEMM of the step: bf16 goes through the direct-to-LDS kernel with a
-// per-shape tile/split plan, fp32 through the register-staged kernel.
+// Plan of a bf16 GEMM.  The large tiles copy bias, gate and scale vectors to
+// LDS 16 bytes at a time; vectors that are not aligned for that stay with the
+// small tiles, whose vector loads need 4 bytes.
+rc::GemmPlan plan(const rc_ctx *c, int M, int N, int K, size_t part_floats, int epi) {
+  return c->vec16 ? rc::plan_gemm(M, N, K, part_floats, epi) : rc::plan_gemm_small(M, N, K, part_floats);
+}
+
+// One GEMM of the step: bf16 by plan, a split one with its sum in a second
+// kernel; fp32 by its own kernel.
 template <typename T>
 rc_status gemm(rc_ctx *c, int cls, const rc::GemmArgs &g, int epi, float *part, size_t part_floats, hipStream_t s,
                const rc::LnNext *ln = nullptr, bool *ln_done = nullptr) {
   if (ln_done) *ln_done = false;
   if constexpr (sizeof(T) == 2) {
-    const rc::GemmPlan pl = rc::plan_gemm(g.M, g.N, g.K, part ? part_floats : 0, epi);
+    const rc::GemmPlan pl = plan(c, g.M, g.N, g.K, part ? part_floats : 0, epi);
     RC_TRY(timed(c, cls, s, [&] {
       return pl.big ? rc::launch_gemm3(g, epi, pl, part, s) : rc::launch_gemm2(g, epi, pl, part, s);
     }));
@@ -406,7 +414,7 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
   int fold_nt = 0;
   bool fold_uv = false;
   if (sizeof(T) == 2) {
-    const rc::GemmPlan px = rc::plan_gemm(R, C, C, gpf, rc::EPI_RESID), p1 = rc::plan_gemm(R, F, C, gpf, rc::EPI_GELU);
+    const rc::GemmPlan px = plan(c, R, C, C, gpf, rc::EPI_RESID), p1 = plan(c, R, F, C, gpf, rc::EPI_GELU);
     const int tile = px.big ? 144 : px.bn;  // producer's statistics tiles
     if (px.splits == 1 && p1.splits == 1 && C % tile == 0 && C / tile <= rc::kFoldMaxTiles) fold_nt = C / tile;
     fold_uv = fold_nt && p1.big;
@@ -851,6 +859,10 @@ rc_status rc_create(const rc_model_config *cfg, const rc_weights *w, rc_ctx **ou
   c->M = cfg->text_len;
   c->Mp = (cfg->text_len + 63) / 64 * 64;
   c->esz = cfg->dtype == RC_BF16 ? 2 : 4;
+  c->vec16 = cfg->token_mode || (aligned16(w->cap_b1) && aligned16(w->cap_b2));
+  for (const rc_layer_weights &lw : c->layers)
+    for (const float *v : {lw.qkv_b, lw.proj_b, lw.xq_b, lw.xkv_b, lw.xproj_b, lw.fc1_b, lw.fc2_b, lw.sst})
+      c->vec16 = c->vec16 && aligned16(v);
   *out = c;
   return RC_OK;
 }

@@ -745,7 +745,7 @@ static void launch_reduce(const GemmArgs &a, int epi, int splits, const float *p
 // 4x2-wave 128x128 QKV tiles (16.3 against 16.8 us), nothing for the
 // 2x4-wave MLP-up tiles.  Two K groups of 2x2 waves beat one group of 2x4
 // for 64x128 tiles at ~400 rows (13.3 against 13.6 us).
-static GemmPlan plan_small(int M, int N, int K, size_t partial_cap_floats) {
+GemmPlan plan_gemm_small(int M, int N, int K, size_t partial_cap_floats) {
   GemmPlan p{64, 128, 1, 1, 2, 2, 2, false};
   const int nk = K / G2_BK;
   const long tn = N / 128;
@@ -811,7 +811,7 @@ static GemmPlan plan_small(int M, int N, int K, size_t partial_cap_floats) {
 // 175 -> 142, 40 -> 28.5 at 2458; MLP-down 74 -> 50 at 4096 and 247 -> 170;
 // out-projections 27 -> 22.5 and 82 -> 70.
 GemmPlan plan_gemm(int M, int N, int K, size_t partial_cap_floats, int epi) {
-  const GemmPlan small = plan_small(M, N, K, partial_cap_floats);
+  const GemmPlan small = plan_gemm_small(M, N, K, partial_cap_floats);
   if (epi == EPI_TEXTKV || N % 144 || K % 64 || M < 256) return small;
   const bool down = K >= 2048 && epi == EPI_RESID;
   const double t64 = std::ceil(M / 64.0) * (N / 128.0), t128 = std::ceil(M / 128.0) * (N / 128.0);

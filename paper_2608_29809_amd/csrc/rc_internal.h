@@ -129,6 +129,9 @@ struct GemmPlan {
 // Tiles, split and kernel of a bf16 GEMM with epilogue `epi`; the folded
 // MLP-up epilogue plans as EPI_GELU.
 GemmPlan plan_gemm(int M, int N, int K, size_t partial_cap_floats, int epi);
+// The same without launch_gemm3's tiles, whose column vectors (bias, gates,
+// fold_scale, fold_u, fold_v) must be 16-byte aligned.
+GemmPlan plan_gemm_small(int M, int N, int K, size_t partial_cap_floats);
 // LayerNorm + modulation of the next block applied to the rows a residual
 // GEMM has just completed: out = E(LN(X) * (1 + scale) + shift) with shift and
 // scale = rows shift_row and shift_row+1 of sst + t0.

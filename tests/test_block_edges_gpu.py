@@ -6,7 +6,7 @@ import torch
 
 import oracle as O
 import synth
-from _cases import download_slot, relerr, upload_slot
+from _cases import download_slot, gemm_plan, relerr, upload_slot
 
 pytestmark = pytest.mark.gpu
 
@@ -74,6 +74,46 @@ def test_large_gemm_tiles(rows):
     (256x288 tiles, one row short of a whole number of row blocks)."""
     print("large tiles", rows, flush=True)
     _block(64, 64, [rows], seed=rows)
+
+
+def test_vectors_aligned_to_4_bytes():
+    """Biases and modulation tables that begin 4 bytes past a 16-byte boundary
+    (views into a packed buffer, which rc_create takes), at a row count whose
+    GEMMs take large tiles with aligned ones: the result is the oracle's."""
+    import ctypes
+
+    from paper_2608_29809_amd import abi
+    print("vectors aligned to 4 bytes", flush=True)
+    s = synth.ModelShape(layers=1, text_dim=1152, grid_h=64, grid_w=64, dtype="bf16", token_mode=True)
+    W = synth.make_weights(s, seed=6, stress=True)
+    rng = np.random.default_rng(6)
+    idx = np.sort(rng.choice(s.tokens, 1009, replace=False)).astype(np.int32)
+    assert gemm_plan(1009, 4608, 1152, "gelu")[0]
+    slot = synth.make_cache_slot(s, 1, 6)
+    x = synth.bf16_round(rng.standard_normal((1, s.tokens, s.hidden)).astype(np.float32))
+    t_vec = rng.standard_normal(s.hidden).astype(np.float32)
+    text = synth.make_text(s, 1, 6)
+    model = RegionCacheModel(s, W)
+    keep = []
+    for f in abi.LAYER_FIELDS:
+        if not f.endswith("_w"):
+            v = torch.from_numpy(np.ascontiguousarray(W["layers"][0][f]).reshape(-1))
+            keep.append(torch.zeros(v.numel() + 1, device="cuda"))
+            keep[-1][1:] = v
+            setattr(model._layers[0], f, keep[-1].data_ptr() + 4)
+    abi.rc_destroy(model.ctx)
+    ctx = ctypes.c_void_p()
+    abi.rc_create(ctypes.byref(model._cfg), ctypes.byref(model._w), ctypes.byref(ctx))
+    model.ctx = ctx
+    cache = model.alloc_cache(1, 1)
+    upload_slot(model, cache, 0, slot)
+    model.reuse_step(cache, 0, ActiveSet.from_lists([idx]), model.to_storage(x), 0, -1,
+                     model.prepare_text(model.to_storage(text)), t_vec=torch.from_numpy(t_vec).cuda())
+    torch.cuda.synchronize()
+    got = download_slot(cache, 0, 1, 1)
+    X, K, V, H, _ = O.reuse_block_tokens(s, W, x[0], idx, t_vec, text[0], slot["K"][0, 0], slot["V"][0, 0], slot["H"][0, 0])
+    assert relerr(got["H"][0, 0][idx], np.asarray(H)[idx]) < 2e-2
+    assert relerr(got["K"][0, 0], K) < 2e-2 and relerr(got["V"][0, 0], V) < 2e-2
 
 
 @pytest.mark.parametrize("sign", [1.0, -1.0])
