@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
   const int g32 = lane >> 5, r32 = lane & 31;
   // column panels share an XCD's L2: the row tiles of a panel are consecutive
   const int T = gridDim.x * gridDim.y, L = xcd_logical_id(blockIdx.x + gridDim.x * blockIdx.y, T);
-  const int m0 = (L % gridDim.y) * GF_BM, n0 = (L / gridDim.y) * BN;
+  const int m0 = (L % gridDim.x) * GF_BM, n0 = (L / gridDim.x) * BN;
   const float *A = (const float *)g.A, *W = (const float *)g.W;
   const int nk = g.K / GF_K;
   const float *src[NL];
@@ -146,8 +146,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
   }
 }
 
+// Row tiles along x: y ends at 65536, which 32-row tiles pass at two million
+// rows (128 chains of 2048 px).
+dim3 gemm_f32_grid(int M, int N, int bn) { return dim3((M + GF_BM - 1) / GF_BM, N / bn); }
+
 template <int BN> static hipError_t launch_f32(const GemmArgs &a, int epi, hipStream_t s) {
-  const dim3 grid(a.N / BN, (a.M + GF_BM - 1) / GF_BM), block(256);
+  const dim3 grid = gemm_f32_grid(a.M, a.N, BN), block(256);
   switch (epi) {
     case EPI_STORE: rc_launch(gemm_f32_kernel<BN, EPI_STORE>, grid, block, 0, s, a); break;
     case EPI_GELU: rc_launch(gemm_f32_kernel<BN, EPI_GELU>, grid, block, 0, s, a); break;

@@ -1,5 +1,25 @@
-"""The tile choice of the bf16 GEMMs (host code of the library)."""
+"""Tile choice and grids of the GEMMs (host code of the library)."""
+import ctypes as C
+
+import pytest
+
 from _cases import gemm_plan
+
+
+class _Dim3(C.Structure):
+    _fields_ = [("x", C.c_uint32), ("y", C.c_uint32), ("z", C.c_uint32)]
+
+
+@pytest.mark.parametrize("rows", [1, 33, 16384, 65536 * 32, 65536 * 32 + 1, 7500000])
+def test_f32_grid_within_the_device_limits(rows):
+    """Up to the rows that 288 GB hold (about 37 KB of workspace each)."""
+    from paper_2608_29809_amd import abi
+    f = abi.LIB._ZN2rc13gemm_f32_gridEiii
+    f.restype, f.argtypes = _Dim3, [C.c_int] * 3
+    for N, bn in ((1152, 32), (1152, 64), (4608, 32), (4608, 64)):
+        g = f(rows, N, bn)
+        assert g.x * 32 >= rows > (g.x - 1) * 32 and g.y * bn == N and g.z == 1
+        assert g.x * 256 < 2 ** 31 and g.y <= 65536
 
 
 def test_plan_is_steady_in_the_row_count():
