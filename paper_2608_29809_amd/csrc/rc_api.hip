@@ -718,7 +718,7 @@ rc_status run_text(rc_ctx *c, const void *txt, int B, void *text_kv, void *ws, s
   g.A = y; g.M = B * M; g.N = 2 * C; g.K = C; g.lda = C;
   g.text_len = M; g.text_pad = c->Mp; g.tkv_chain_stride = (long long)text_kv_elems_per_entry(c); g.hidden = C;
   const long long layer_stride = (long long)B * text_kv_elems_per_entry(c);
-  if (sizeof(T) == 2) {
+  if constexpr (sizeof(T) == 2) {
     for (int l0 = 0; l0 < c->L; l0 += rc::TextLayers::kLayers) {
       rc::TextLayers tl{};
       const int nl = std::min(c->L - l0, rc::TextLayers::kLayers);
@@ -730,13 +730,13 @@ rc_status run_text(rc_ctx *c, const void *txt, int B, void *text_kv, void *ws, s
       g.tkv = (T *)text_kv + l0 * layer_stride;
       RC_TRY(timed(c, RC_KC_GEMM, s, [&] { return rc::launch_text_kv(g, tl, nl, s); }));
     }
-    return RC_OK;
-  }
-  for (int l = 0; l < c->L; ++l) {
-    g.W = c->layers[l].xkv_w;
-    g.bias = c->layers[l].xkv_b;
-    g.tkv = (T *)text_kv + l * layer_stride;
-    RC_TRY(gemm<T>(c, RC_KC_GEMM, g, rc::EPI_TEXTKV, nullptr, 0, s));
+  } else {
+    for (int l = 0; l < c->L; ++l) {
+      g.W = c->layers[l].xkv_w;
+      g.bias = c->layers[l].xkv_b;
+      g.tkv = (T *)text_kv + l * layer_stride;
+      RC_TRY(gemm<T>(c, RC_KC_GEMM, g, rc::EPI_TEXTKV, nullptr, 0, s));
+    }
   }
   return RC_OK;
 }

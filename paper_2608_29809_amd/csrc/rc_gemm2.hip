@@ -74,13 +74,11 @@ __device__ __forceinline__ void epi_store(const GemmArgs &g, int m, int n, float
       ((bf16 *)(part == 1 ? g.kslot : g.vslot))[cb + ((size_t)hh * g.tokens + tok) * kHeadDim + dd] = (bf16)v;
     }
   } else if (EPI == EPI_TEXTKV) {
+    // (the transposed values; the keys go through epi4)
     const int b = m / g.text_len, t = m - b * g.text_len;
     bf16 *base = (bf16 *)g.tkv + (size_t)b * g.tkv_chain_stride;
     const size_t half = (size_t)(g.hidden / kHeadDim) * g.text_pad * kHeadDim;
-    if (part == 0)
-      base[((size_t)hh * g.text_pad + t) * kHeadDim + dd] = (bf16)v;
-    else
-      base[half + ((size_t)hh * kHeadDim + dd) * g.text_pad + t] = (bf16)v;
+    base[half + ((size_t)hh * kHeadDim + dd) * g.text_pad + t] = (bf16)v;
   }
 }
 
@@ -156,7 +154,7 @@ __device__ __forceinline__ void col_info(const GemmArgs &g, int n, float &bn, fl
   part = 0;
   hh = 0;
   dd = 0;
-  if (EPI == EPI_QKV || EPI == EPI_TEXTKV) {
+  if (EPI == EPI_QKV) {
     part = n / g.hidden;
     const int c = n - part * g.hidden;
     hh = c / kHeadDim;
@@ -704,7 +702,6 @@ static void launch_g2(const GemmArgs &a, int epi, int splits, float *partial, hi
       break;
     case EPI_RESID: RC_G2(EPI_RESID); break;
     case EPI_QKV: RC_G2(EPI_QKV); break;
-    case EPI_TEXTKV: RC_G2(EPI_TEXTKV); break;
   }
 #undef RC_G2
 }
@@ -718,7 +715,6 @@ static void launch_reduce(const GemmArgs &a, int epi, int splits, const float *p
     case EPI_GELU: RC_RD(EPI_GELU); break;
     case EPI_RESID: RC_RD(EPI_RESID); break;
     case EPI_QKV: RC_RD(EPI_QKV); break;
-    case EPI_TEXTKV: RC_RD(EPI_TEXTKV); break;
   }
 #undef RC_RD
 }
@@ -812,7 +808,7 @@ GemmPlan plan_gemm_small(int M, int N, int K, size_t partial_cap_floats) {
 // out-projections 27 -> 22.5 and 82 -> 70.
 GemmPlan plan_gemm(int M, int N, int K, size_t partial_cap_floats, int epi) {
   const GemmPlan small = plan_gemm_small(M, N, K, partial_cap_floats);
-  if (epi == EPI_TEXTKV || N % 144 || K % 64 || M < 256) return small;
+  if (N % 144 || K % 64 || M < 256) return small;
   const bool down = K >= 2048 && epi == EPI_RESID;
   const double t64 = std::ceil(M / 64.0) * (N / 128.0), t128 = std::ceil(M / 128.0) * (N / 128.0);
   const double mn = (double)M * N, norm = down ? 2.0 + mn * 6.0 / 4e6 : 0.0;
@@ -829,7 +825,8 @@ GemmPlan plan_gemm(int M, int N, int K, size_t partial_cap_floats, int epi) {
   for (const Tile &t : tiles)
     for (int sp = 1; sp <= 4; sp *= 2) {
       if (N % t.bn || K % (32 * t.kg * sp) || (epi == EPI_QKV && (N / 3) % t.bn)) continue;
-      if (sp > 1 && (!down || (size_t)sp * M * N > partial_cap_floats)) continue;
+      // (split, the other tiles' estimates are never the least: no kernels for them)
+      if (sp > 1 && (!down || t.bm != 128 || t.bn != 144 || (size_t)sp * M * N > partial_cap_floats)) continue;
       const double wgs = std::ceil((double)M / t.bm) * (N / t.bn) * sp, nst = (double)K / (32 * t.kg * sp);
       const double rounds = std::ceil(wgs / t.slots);
       double ends = rounds * t.ends[kind];
@@ -849,7 +846,8 @@ GemmPlan plan_gemm(int M, int N, int K, size_t partial_cap_floats, int epi) {
 
 hipError_t launch_gemm2(const GemmArgs &a, int epi, const GemmPlan &pl, float *partial, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  if ((pl.bn != 128 && pl.bn != 64) || a.N % pl.bn || a.K % (G2_BK * pl.splits * pl.kg)) return hipErrorInvalidValue;
+  if ((pl.bn != 128 && pl.bn != 64) || a.N % pl.bn || a.K % (G2_BK * pl.splits * pl.kg) || epi == EPI_TEXTKV)
+    return hipErrorInvalidValue;
   const bool split = pl.splits > 1;
   // the folded LayerNorm needs the whole K range in one launch and the
   // producer's per-tile statistics (equal column counts, at most kFoldMaxTiles)
@@ -859,9 +857,9 @@ hipError_t launch_gemm2(const GemmArgs &a, int epi, const GemmPlan &pl, float *p
   // the fold's producer writes its statistics from the one-pass row epilogue
   if (epi == EPI_RESID && a.fold_stats && (split || a.fold_nt != a.N / pl.bn || !a.xt || !a.fold_extra))
     return hipErrorInvalidValue;
-  // 4-wave K groups: 128 rows = 2x2 waves of 64x64, 64 rows = 2x2 of 32x64,
-  // 32 rows = 1x4 of 32x32, 64x64 tiles = 2x2 of 32x32; 8-wave: 128 rows =
-  // 4x2 of 32x64 or 2x4 of 64x32, 64 rows = 2x4 of 32x32
+  // 4-wave K groups: 64 rows = 2x2 waves of 32x64, 32 rows = 1x4 of 32x32,
+  // 64x64 tiles = 2x2 of 32x32; 2-wave: 32x64 tiles = 1x2 of 32x32; 8-wave:
+  // 128 rows = 4x2 of 32x64 or 2x4 of 64x32, 64 rows = 2x4 of 32x32
 #define RC_G2(BMV, BNV, KGV, STG, WM_, WN_)                                                   \
   {                                                                                          \
     if (split) launch_g2<BMV, BNV, STG, KGV, WM_, WN_, true>(a, epi, pl.splits, partial, s); \
@@ -872,12 +870,8 @@ hipError_t launch_gemm2(const GemmArgs &a, int epi, const GemmPlan &pl, float *p
     case 1280641222: RC_G2(64, 128, 1, 2, 2, 2) break;
     case 1280642322: RC_G2(64, 128, 2, 3, 2, 2) break;
     case 1280641324: RC_G2(64, 128, 1, 3, 2, 4) break;
-    case 1280321314: RC_G2(32, 128, 1, 3, 1, 4) break;
     case 1280322314: RC_G2(32, 128, 2, 3, 1, 4) break;
-    case 1280323214: RC_G2(32, 128, 3, 2, 1, 4) break;
-    case 1281281222: RC_G2(128, 128, 1, 2, 2, 2) break;
     case 1281281242: RC_G2(128, 128, 1, 2, 4, 2) break;
-    case 1281281342: RC_G2(128, 128, 1, 3, 4, 2) break;
     case 1281281324: RC_G2(128, 128, 1, 3, 2, 4) break;
     case 640642422: RC_G2(64, 64, 2, 4, 2, 2) break;
     case 640322312: RC_G2(32, 64, 2, 3, 1, 2) break;

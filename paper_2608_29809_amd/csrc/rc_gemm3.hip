@@ -40,7 +40,8 @@ template <int N> __device__ __forceinline__ void wait_vm_g3() {
 // 16-byte chunk swizzle of a ring row of 64 KG bytes: the 16 rows of a
 // fragment read touch all 64 banks once.
 template <int KG> __device__ __forceinline__ int swz3(int row) {
-  return KG == 1 ? (row >> 2) & 3 : KG == 2 ? (row >> 1) & 7 : row & 15;
+  static_assert(KG == 1 || KG == 2, "ring rows of 64 or 128 bytes");
+  return KG == 1 ? (row >> 2) & 3 : (row >> 1) & 7;
 }
 
 template <int FM, int WGM, int WGN, int KG, int S, int EPI, bool SPLIT>
@@ -493,26 +494,24 @@ static void launch_g3(const GemmArgs &a, int epi, int splits, float *partial, hi
 
 hipError_t launch_gemm3(const GemmArgs &a, int epi, const GemmPlan &pl, float *partial, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  if (a.N % pl.bn || a.K % (32 * pl.kg * pl.splits) || epi == EPI_TEXTKV || (pl.splits > 1 && epi != EPI_RESID))
+  if (a.N % pl.bn || a.K % (32 * pl.kg * pl.splits) || epi == EPI_TEXTKV ||
+      (pl.splits > 1 && (epi != EPI_RESID || pl.bm != 128 || pl.bn != 144)))
     return hipErrorInvalidValue;
   if (epi == EPI_QKV && a.hidden % pl.bn) return hipErrorInvalidValue;
   if (epi == EPI_GELU_FOLD &&
       (a.fold_nt <= 0 || a.fold_nt > kFoldMaxTiles || a.K % a.fold_nt || !a.fold_stats || !a.fold_u || !a.fold_v))
     return hipErrorInvalidValue;
   if (epi == EPI_RESID && a.fold_stats && (pl.splits > 1 || a.fold_nt != a.N / G3_WN || !a.xt)) return hipErrorInvalidValue;
-#define RC_G3(FM_, WM_, WN_, KG_, S_)                                                            \
-  {                                                                                              \
-    if (pl.splits > 1) launch_g3<FM_, WM_, WN_, KG_, S_, true>(a, epi, pl.splits, partial, s);   \
-    else launch_g3<FM_, WM_, WN_, KG_, S_, false>(a, epi, 1, nullptr, s);                        \
-  }
   switch (pl.bm * 1000 + pl.bn) {
-    case 256288: RC_G3(4, 4, 2, 1, 4) break;
-    case 256144: RC_G3(4, 4, 1, 2, 3) break;
-    case 128144: RC_G3(2, 4, 1, 2, 4) break;
-    case 128288: RC_G3(4, 2, 2, 1, 3) break;
+    case 256288: launch_g3<4, 4, 2, 1, 4, false>(a, epi, 1, nullptr, s); break;
+    case 256144: launch_g3<4, 4, 1, 2, 3, false>(a, epi, 1, nullptr, s); break;
+    case 128144:
+      if (pl.splits > 1) launch_g3<2, 4, 1, 2, 4, true>(a, epi, pl.splits, partial, s);
+      else launch_g3<2, 4, 1, 2, 4, false>(a, epi, 1, nullptr, s);
+      break;
+    case 128288: launch_g3<4, 2, 2, 1, 3, false>(a, epi, 1, nullptr, s); break;
     default: return hipErrorInvalidValue;
   }
-#undef RC_G3
   return hipGetLastError();
 }
 
