@@ -14,9 +14,10 @@ if torch.cuda.is_available():
     from paper_2608_29809_amd.runtime import ActiveSet, RegionCacheModel
 
 
-def _block(gh, gw, counts, seed, edit=None):
-    """A bf16 reuse block of len(counts) chains over gh x gw tokens; returns
-    (per chain) the errors of H and of the attention's own change of H."""
+def _block(gh, gw, counts, seed, edit=None, chains=None):
+    """A bf16 reuse block of len(counts) chains over gh x gw tokens, `chains`
+    of them (all by default) compared with the oracle: H of the active rows,
+    K and V of the slot."""
     s = synth.ModelShape(layers=1, text_dim=1152, grid_h=gh, grid_w=gw, dtype="bf16", token_mode=True)
     W = synth.make_weights(s, seed=seed, stress=True)
     if edit:
@@ -38,7 +39,7 @@ def _block(gh, gw, counts, seed, edit=None):
                      t_vec=torch.from_numpy(t_vec).cuda())
     torch.cuda.synchronize()
     got = download_slot(cache, 0, 1, B)
-    for b in range(B):
+    for b in range(B) if chains is None else chains:
         if not counts[b]:
             continue
         X, K, V, H, _ = O.reuse_block_tokens(s, W, x[b], idx[b], t_vec, text[b], slot["K"][0, b], slot["V"][0, b],
@@ -68,12 +69,33 @@ def test_many_chains(counts):
 
 @pytest.mark.parametrize("rows", [1009, 2449, 3969])
 def test_large_gemm_tiles(rows):
-    """Row counts that take the large GEMM tiles, each with a last row tile of
-    a few rows less than full: the MLP at 1009 rows (128x144 tiles, its
-    MLP-down split in four), QKV in 256x144 tiles at 2449, every GEMM at 3969
-    (256x288 tiles, one row short of a whole number of row blocks)."""
+    """Row counts that take large GEMM tiles, each with a last row tile that is
+    not full: the MLP at 1009 rows (128x144 tiles, its MLP-down split in four),
+    QKV in 256x144 and MLP-down in 128x144 tiles at 2449, every GEMM at 3969
+    (QKV and MLP-up in 256x288 tiles, the last with 129 rows, the others in
+    128x144, the last with one)."""
     print("large tiles", rows, flush=True)
     _block(64, 64, [rows], seed=rows)
+
+
+# large tile (rows, columns) of QKV, both out-projections, the cross query,
+# MLP-up and MLP-down, None for the small ones
+@pytest.mark.parametrize("rows,tiles", [
+    (2045, (None, None, None, (256, 144), (128, 144))), (6001, (None, (256, 144), (256, 144), (256, 144), (256, 144))),
+    (11003, (None, (128, 144), (256, 288), (128, 288), (128, 144))),
+    (16381, ((256, 288), (256, 288), (256, 288), (128, 288), (256, 288)))])
+def test_large_gemm_tiles_of_many_rows(rows, tiles):
+    """The other large tiles, each with a last row tile that is not full: many
+    chains of 64 tokens (the GEMMs see rows only), of which those at the tile
+    borders, the first and the last are compared."""
+    shapes = ((3456, 1152, "qkv"), (1152, 1152, "resid"), (1152, 1152, "store"), (4608, 1152, "gelu"), (1152, 4608, "resid"))
+    for (N, K, epi), tile in zip(shapes, tiles):
+        p = gemm_plan(rows, N, K, epi)
+        assert (p[1:3] if p[0] else None) == tile, (N, K, epi, p)
+    print("large tiles of many rows", rows, flush=True)
+    counts = [64] * (rows // 64) + [rows % 64]
+    n = len(counts)
+    _block(8, 8, counts, seed=rows, chains=sorted({0, 1, 2, 3, 4, n // 2, n - 5, n - 3, n - 2, n - 1}))
 
 
 def test_vectors_aligned_to_4_bytes():
