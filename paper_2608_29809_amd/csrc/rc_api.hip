@@ -407,10 +407,11 @@ rc_status run_step(rc_ctx *c, const rc_cache_view *cache, int step, const rc_ste
   // bf16: the MLP-up LayerNorm folds into the GEMMs on either side of it
   // when both run unsplit.  The cross out-projection's epilogue writes each
   // row's mean and sum of squared deviations over its column tile and the
-  // modulated copy x~ = x (1 + scale); the MLP-up GEMM takes four more A rows
-  // per tile, (1 + scale) and shift as bf16 pairs, and applies
-  // h W^T = r (x~ W^T - mean u) + v after its K loop (u, v: the products of
-  // those rows).
+  // modulated copy x~ = x (1 + scale); the MLP-up GEMM applies
+  // h W^T = r (x~ W^T - mean u) + v after its K loop.  u = W (1 + scale) and
+  // v = W shift: the small tiles take four more A rows each, (1 + scale) and
+  // shift as bf16 pairs; for the large ones launch_fold_uv makes them once per
+  // step for all blocks.
   int fold_nt = 0;
   bool fold_uv = false;
   if (sizeof(T) == 2) {

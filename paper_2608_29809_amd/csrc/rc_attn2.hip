@@ -383,7 +383,8 @@ __global__ __launch_bounds__(512, 1) void attn2q_kernel(AttnArgs a) {
 // all text keys: the scores of the (at most four) 32-key sub-tiles stay in
 // registers, one maximum, one pass of exponentials, one P.V chain (operand
 // layouts as above; V^T rows are n_keys wide, their 16-byte chunks swizzled by
-// the row).  37 KB of LDS: four workgroups per CU.
+// the row).  37 KB of LDS would let four workgroups share a CU; 172 registers
+// hold it to two (152 with maps: three).
 // Measured, fused -> projection + this: 4096 rows 46 -> 29 us, 16384 rows
 // 170 -> 89 (this kernel 42.6: 1.8 TB/s of queries and outputs), 2458 rows
 // 35 -> 26, 1639 rows 23.4 -> 21.4.

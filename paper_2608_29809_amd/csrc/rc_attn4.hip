@@ -29,18 +29,21 @@
 // goes as three bf16 parts (24 bits: exactly) into the query dims 72..74,
 // which meet ones in the padded key dims.  Probabilities below 2^-126 are
 // lost, at most 2^-72 of an accepted denominator for 16384 keys, and values
-// above 2^-86 keep their precision.
+// above 2^-86 keep their precision.  The restart costs what it repeats: with
+// every workgroup in it, 723 queries of 4096 keys and their combine take 53.6
+// us instead of 30.2, 4096 of 4096 190 instead of 85, 16384 of 16384 2.5 ms
+// instead of 1.14 (logits beyond 55, or all of a query's below -28).
 //
 // A wave holds QH = 2 or 1 halves of 32 queries.  What bounds the kernel: for
 // many queries the matrix core at the clock that the power limit leaves (63 %
 // of the matrix cycles at 1.84 GHz for 16384 x 16384: 1.3 PFLOP/s with the
-// padding, the rate of a large library GEMM here).  QH = 2 reads each key and
-// value fragment from LDS once for 64 queries: LDS reads and matrix clocks
-// per 32x32 unit are 9.7 KB and 320, against 19.5 KB for QH = 1, which the
-// eight waves of a CU cannot get from LDS (128 bytes per clock) in the same
-// time.  For a few hundred queries the fixed time bounds it (about 4 us to
-// the first tile, 1.2 us of stores), and QH = 1 gives it more workgroups with
-// shorter ends.  The work is written as pairs of 32x32 units so that the
+// padding, the rate of a large library GEMM here).  A unit of 32 queries and
+// 32 keys takes 320 matrix clocks of its SIMD and, for QH = 1, 10 KB of key and
+// value fragments: the four SIMDs of a CU read 40 KB in that time, all that LDS
+// gives (128 bytes per clock).  QH = 2 reads each fragment once for 64 queries,
+// half of that.  For a few hundred queries the fixed time bounds it (about 4 us
+// to the first tile, 1.2 us of stores), and QH = 1 gives it more workgroups
+// with shorter ends.  The work is written as pairs of 32x32 units so that the
 // exponentials of one run under the matrix instructions of the other; the
 // groups are kept apart by scheduling barriers, and a wave has issue priority
 // over the other wave of its SIMD in its PV half (23.3 against 24.1 us at 723
@@ -48,9 +51,10 @@
 // the score half gives half of that).
 //
 // Measured per launch, before (one 32-query form with a running maximum) and
-// now: 16384 queries of 16384 keys 1371 -> 1048 us, 2458 of 16384 232 -> 183,
-// 4096 of 4096 95.4 -> 80.4, 1639 in four chains of 4096 50 -> 44.6, 723 of
-// 4096 23.8 -> 23.3 us.
+// now: 16384 queries of 16384 keys 1411 -> 1073 us, 2458 of 16384 236 -> 182,
+// 4096 of 4096 97.3 -> 83.3, 1640 in four chains of 4096 50.0 -> 44.8, 723 of
+// 4096 23.6 -> 21.7 us; 300 chains of 64 keys 39.4 -> 40.3 us, one query of
+// 1024 keys 4.9 -> 5.3 us.
 #include "rc_common.h"
 #include "rc_launch.h"
 #include "rc_internal.h"
@@ -486,11 +490,15 @@ hipError_t launch_attn_combine_norm(const void *Opart, const float *ML, void *O,
 
 // Query halves per wave and key splits: the pair with the least estimated
 // time.  A tile of 64 keys takes a CU's two workgroups 1.07 us at QH = 1 and
-// 1.85 at QH = 2 (measured at 4096 keys), a lone workgroup about 0.65 of that;
-// the ends (first tile, stores) take 6.5 and 9 us; a combine 4 us and its
-// bytes at about 4 TB/s.  At 723 queries of 4096 keys: 23.3 + 4.3 us for QH = 1
-// in five splits, 26.8 + 4.4 for QH = 2 in eight; at 1639 in four chains 46.8
-// (QH = 1) and 44.6 (QH = 2, four splits).
+// 1.85 at QH = 2, a lone workgroup about 0.65 of that; the ends (first tile,
+// stores) take 6.5 and 9 us; a combine 4 us and its bytes at about 4 TB/s.
+// These were fitted before the tile copies lost their branches, which took
+// about 6 % off QH = 1 and 1 % off QH = 2, so near the line QH = 2 is taken
+// where QH = 1 has become as fast or a little faster (best of each with its
+// combine, us, launches included): 723 queries of 4096 keys 29.3 (QH = 1, five
+// splits) and 30.8; 1639 in one chain 45.0 (two) and 47.6, 48.4 as planned; in
+// four chains 49.0 and 49.6, 50.1 as planned; 2458 67.0 and 62.2; 4096 81.6 and
+// 81.8; 1639 of 16384 141 and 137, 16384 of 16384 1192 and 1047.
 AttnPlan plan_attention(const int *counts, int n_chains, int heads, int n_keys, long max_split_rows) {
   const int n_tiles = n_keys / A4_BK;
   long rows = 0;

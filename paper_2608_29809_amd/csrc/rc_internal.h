@@ -56,15 +56,17 @@ struct GemmArgs {
   // squared deviations of the updated x go to fold_stats[m * fold_nt + tile];
   // the workgroups of row tile 0 write 1 + scale and shift into fold_extra,
   // each as two rows: its bf16 rounding, then the bf16 rounding of the
-  // remainder.  Consumer (EPI_GELU_FOLD): a BM-row tile holds BM - 4 rows of
-  // A (= x~) and fold_extra's four rows, whose products summed in pairs are
-  // u and v; fold_stats is merged per row (in tile order) into mu and r.
+  // remainder.  Consumer (EPI_GELU_FOLD): fold_stats is merged per row (in
+  // tile order) into mu and r.  u and v: in launch_gemm2 a BM-row tile holds
+  // BM - 4 rows of A (= x~) and fold_extra's four rows, whose products summed
+  // in pairs they are; launch_gemm3 takes them from fold_u and fold_v, which
+  // launch_fold_uv has made for all blocks of the step.
   const float *fold_scale[2];  // scale = fold_scale[0] + fold_scale[1], [N] each (producer)
   const float *fold_shift[2];  // shift = fold_shift[0] + fold_shift[1] (producer)
   float2 *fold_stats;          // [M][fold_nt] (mean, sum of squared deviations)
   int fold_nt;                 // producer column tiles (K / fold_nt columns each)
-  void *fold_extra;            // [4][C] E
-  const float *fold_u, *fold_v; // [N] u and v (consumer of launch_gemm3, in place of fold_extra)
+  void *fold_extra;            // [4][C] E (consumer of launch_gemm2)
+  const float *fold_u, *fold_v; // [N] u and v (consumer of launch_gemm3)
   float fold_eps;              // consumer
 };
 // most producer column tiles a folded LayerNorm merges per row
