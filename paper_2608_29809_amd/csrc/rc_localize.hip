@@ -125,17 +125,27 @@ hipError_t launch_sum_partials(const float *partial, int n_parts, int n, float *
 }
 
 // Stable compaction by a 1024-thread workgroup of up to 16 x 1024 tokens, of
-// which this thread holds i0 + 1024 k + tid for k < nk, selected where bit k
-// of `on` is set: their numbers go to idx[base ..] in ascending order.  One
-// ballot per 64 tokens, one scan over the counts of all of them; returns the
-// number selected.  cnt: [257] ints of LDS.
-__device__ __forceinline__ int compact_tokens(unsigned on, int nk, int i0, int base, int *idx, int *cnt) {
+// which this thread holds i0 + 1024 k + tid for k < nk (those below `end`),
+// selected where bit k of `on` is set: their numbers go to idx[base ..] in
+// ascending order.  One ballot per 64 tokens, one scan over the counts of all of
+// them; returns the number selected.  cnt: [257] ints of LDS.
+// STREAM: the tokens are chains of N laid end to end, numbered within each, and
+// the chains that begin here get their offsets, from the last wave, whose lane l
+// has chain l, l + 64, ... (b, first token at s) as its next.  word: [256]
+// ballots of LDS.
+template <bool STREAM>
+__device__ __forceinline__ int compact_tokens(unsigned on, int nk, int i0, int base, int *idx, int *cnt, int end = 0,
+                                              int N = 1, int *b = nullptr, unsigned *s = nullptr, int *offsets = nullptr,
+                                              uint64_t *word = nullptr) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t below = lane == 0 ? 0ull : ~0ull >> (64 - lane);
   __syncthreads();  // earlier readers of cnt are done
   for (int k = 0; k < nk; ++k) {
     const uint64_t bal = __ballot((on >> k) & 1u);
-    if (lane == 0) cnt[k * 16 + wave] = __popcll(bal);
+    if (lane == 0) {
+      cnt[k * 16 + wave] = __popcll(bal);
+      if (STREAM) word[k * 16 + wave] = bal;
+    }
   }
   __syncthreads();
   if (wave == 0) {  // exclusive scan of nk * 16 <= 256 counts, four per lane
@@ -160,11 +170,20 @@ __device__ __forceinline__ int compact_tokens(unsigned on, int nk, int i0, int b
     if (lane == 63) cnt[256] = inc;
   }
   __syncthreads();
+  const int step = STREAM ? 1024 % N : 1024;
+  int tok = STREAM ? (i0 + tid) % N : i0 + tid;
   for (int k = 0; k < nk; ++k) {
     const bool sel = (on >> k) & 1u;
     const uint64_t bal = __ballot(sel);
-    if (sel) idx[base + cnt[k * 16 + wave] + __popcll(bal & below)] = i0 + k * 1024 + tid;
+    if (sel) idx[base + cnt[k * 16 + wave] + __popcll(bal & below)] = tok;
+    tok += step;
+    if (STREAM) tok -= tok >= N ? N : 0;
   }
+  if (STREAM && wave == 15)
+    for (; *s < (unsigned)(i0 + min(end - i0, nk * 1024)); *b += 64, *s += 64u * N) {
+      const int r = (int)*s - i0;
+      offsets[*b] = base + cnt[r >> 6] + __popcll(word[r >> 6] & ((1ull << (r & 63)) - 1));
+    }
   return cnt[256];
 }
 
@@ -185,42 +204,45 @@ __device__ __forceinline__ float row16_fmin(float v) {
 // ballots of the waves), so a token's neighbourhood is a shift of a word or
 // two per row.  With a pass over memory for each column's range and
 // another for its threshold the kernel took 25.8 us at 64x64 tokens and six
-// columns, and the compaction another 4.7.
+// columns, and the compaction another 4.7.  A small call pays for fetching code
+// that runs once, so the column count ND is the kernel's: for all counts in one
+// kernel a call with one column took 2 to 6 us more than those two passes on
+// grids of up to 1024 tokens.
 constexpr int kLocTok = 4;  // tokens of a thread loaded together
-__global__ __launch_bounds__(1024) void localize_kernel(const float *maps, int gh, int gw, int n_delta,
-                                                        float threshold, int radius, uint8_t *mask, int *idx,
-                                                        int *offsets) {
+template <int ND>
+__global__ __launch_bounds__(1024) void localize_kernel(const float *maps, int gh, int gw, float threshold, int radius,
+                                                        uint8_t *mask, int *idx, int *offsets) {
   __shared__ uint64_t bits[258];       // selection of 64 tokens each, a spare word past the last
-  __shared__ float red[16][64], range[16];  // per column 2 j: minimum, 2 j + 1: -maximum
+  __shared__ float red[2 * ND][64], range[2 * ND];  // per column 2 j: minimum, 2 j + 1: -maximum
   __shared__ int cnt[257];
   const int b = blockIdx.x, tid = threadIdx.x, N = gh * gw;
   const int lane = tid & 63, wave = tid >> 6;
-  const float *m = maps + (size_t)b * N * n_delta;
+  const float *m = maps + (size_t)b * N * ND;
   const int nk = (N + 1023) / 1024, n_chunk = (nk + kLocTok - 1) / kLocTok;
-  float v[kLocTok][8];
+  float v[kLocTok][ND];
   auto load = [&](int c) {
 #pragma unroll
     for (int k = 0; k < kLocTok; ++k) {
-      const float *p = m + (size_t)min((c * kLocTok + k) * 1024 + tid, N - 1) * n_delta;
+      const float *p = m + (size_t)min((c * kLocTok + k) * 1024 + tid, N - 1) * ND;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[k][j] = j < n_delta ? p[j] : 0.0f;
+      for (int j = 0; j < ND; ++j) v[k][j] = p[j];
     }
   };
-  float lo[8], nhi[8];
+  float lo[ND], nhi[ND];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) lo[j] = nhi[j] = INFINITY;
+  for (int j = 0; j < ND; ++j) lo[j] = nhi[j] = INFINITY;
   for (int c = 0; c < n_chunk; ++c) {
     load(c);
 #pragma unroll
     for (int k = 0; k < kLocTok; ++k)  // (a token past the last is the last again)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int j = 0; j < ND; ++j) {
         lo[j] = fminf(lo[j], v[k][j]);
         nhi[j] = fminf(nhi[j], -v[k][j]);
       }
   }
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
+  for (int j = 0; j < ND; ++j) {
     lo[j] = row16_fmin(lo[j]);
     nhi[j] = row16_fmin(nhi[j]);
     if ((lane & 15) == 0) {
@@ -229,7 +251,7 @@ __global__ __launch_bounds__(1024) void localize_kernel(const float *maps, int g
     }
   }
   __syncthreads();
-  {
+  if (wave < 2 * ND) {
     float r = red[wave][lane];
     r = row16_fmin(r);
     r = fminf(r, __shfl_xor(r, 16, 64));
@@ -238,12 +260,12 @@ __global__ __launch_bounds__(1024) void localize_kernel(const float *maps, int g
   }
   __syncthreads();
   unsigned live = 0;  // columns that select (a constant map selects nothing)
-  float inv[8];
+  float inv[ND];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
+  for (int j = 0; j < ND; ++j) {
     lo[j] = range[2 * j];
     const float hi = -range[2 * j + 1];
-    live |= (unsigned)(j < n_delta && hi > lo[j]) << j;
+    live |= (unsigned)(hi > lo[j]) << j;
     inv[j] = 1.0f / (hi - lo[j]);
   }
   for (int c = 0; c < n_chunk; ++c) {
@@ -253,7 +275,7 @@ __global__ __launch_bounds__(1024) void localize_kernel(const float *maps, int g
       const int i = (c * kLocTok + k) * 1024 + tid;
       bool on = false;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) on = on || (((live >> j) & 1u) && (v[k][j] - lo[j]) * inv[j] >= threshold);
+      for (int j = 0; j < ND; ++j) on = on || (((live >> j) & 1u) && (v[k][j] - lo[j]) * inv[j] >= threshold);
       const uint64_t bal = __ballot(on && i < N);
       if (lane == 0 && i < N) bits[i >> 6] = bal;
     }
@@ -280,7 +302,7 @@ __global__ __launch_bounds__(1024) void localize_kernel(const float *maps, int g
     }
   }
   if (idx) {
-    const int total = compact_tokens(sel, nk, 0, 0, idx, cnt);
+    const int total = compact_tokens<false>(sel, nk, 0, 0, idx, cnt);
     if (tid == 0) {
       offsets[0] = 0;
       offsets[1] = total;
@@ -290,29 +312,45 @@ __global__ __launch_bounds__(1024) void localize_kernel(const float *maps, int g
 
 hipError_t launch_localize(const float *maps, int B, int gh, int gw, int n_delta, float threshold, int radius,
                            uint8_t *mask, int *idx, int *offsets, hipStream_t s) {
-  if ((long)gh * gw > 16384 || (gh * gw) % 64 || n_delta > 8) return hipErrorInvalidValue;
+  if ((long)gh * gw > 16384 || (gh * gw) % 64) return hipErrorInvalidValue;
   int *one = B == 1 ? idx : nullptr;
-  rc_launch(localize_kernel, dim3(B), dim3(1024), 0, s, maps, gh, gw, n_delta, threshold, radius, mask, one, offsets);
+#define RC_LOC(ND) \
+  case ND: rc_launch(localize_kernel<ND>, dim3(B), dim3(1024), 0, s, maps, gh, gw, threshold, radius, mask, one, offsets); break;
+  switch (n_delta) {
+    RC_LOC(1) RC_LOC(2) RC_LOC(3) RC_LOC(4) RC_LOC(5) RC_LOC(6) RC_LOC(7) RC_LOC(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef RC_LOC
   return B == 1 ? hipGetLastError() : launch_compact(mask, B, gh * gw, idx, offsets, s);
 }
 
-// Stable compaction over all chains by one workgroup, up to 16384 tokens of a
-// chain at a time (every mask byte of them is loaded before the first is used).
+// Stable compaction over all chains by one workgroup, 16384 tokens at a time
+// (every mask byte of them is loaded before the first is used).  STREAM: all
+// chains as one sequence of B N tokens, a barrier and a scan per 16384 tokens;
+// else chain by chain, which for short chains takes 1.4 us each: 443 us for 300
+// chains of 64 tokens and 125 for 64 of 1024, as one sequence 72 and 60 (a loop
+// over 1024 tokens of a chain at a time: 194 and 72).
+template <bool STREAM>
 __global__ __launch_bounds__(1024) void compact_kernel(const uint8_t *mask, int B, int N, int *idx, int *offsets) {
   __shared__ int cnt[257];
-  const int tid = threadIdx.x;
-  int base = 0;
-  for (int b = 0; b < B; ++b) {
-    if (tid == 0) offsets[b] = base;
-    for (int i0 = 0; i0 < N; i0 += 16384) {
-      const int nk = min(16, (N - i0 + 1023) / 1024);
+  __shared__ uint64_t word[STREAM ? 256 : 1];
+  const int tid = threadIdx.x, end = STREAM ? B * N : N;  // (at most 32767 x 65535)
+  int base = 0, b = tid & 63;
+  unsigned s = (unsigned)b * N;
+  for (int c = 0; c < (STREAM ? 1 : B); ++c) {
+    if (!STREAM && tid == 0) offsets[c] = base;
+    for (int i0 = 0;;) {
+      const int nk = min(16, (end - i0 + 1023) / 1024);
       unsigned on = 0;
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         const int i = i0 + k * 1024 + tid;
-        on |= (unsigned)(i < N && mask[(size_t)b * N + min(i, N - 1)] != 0) << k;
+        on |= (unsigned)(i < end && mask[(size_t)c * N + min(i, end - 1)] != 0) << k;
       }
-      base += compact_tokens(on, nk, i0, base, idx, cnt);
+      base += STREAM ? compact_tokens<true>(on, nk, i0, base, idx, cnt, end, N, &b, &s, offsets, word)
+                     : compact_tokens<false>(on, nk, i0, base, idx, cnt);
+      if (end - i0 <= 16384) break;  // (before i0 could overflow)
+      i0 += 16384;
     }
   }
   if (tid == 0) offsets[B] = base;
@@ -354,7 +392,11 @@ hipError_t launch_validate_active(const int *offsets, const int *idx, int B, int
 }
 
 hipError_t launch_compact(const uint8_t *mask, int B, int N, int *idx, int *offsets, hipStream_t s) {
-  rc_launch(compact_kernel, dim3(1), dim3(1024), 0, s, mask, B, N, idx, offsets);
+  // one sequence unless a chain fills 16384 tokens by itself (localisation of 32
+  // such chains 275 us one by one, 304 in one sequence) or is the only one
+  // (65535 tokens: 48.7 and 51.9 us)
+  if (B == 1 || N >= 16384) rc_launch(compact_kernel<false>, dim3(1), dim3(1024), 0, s, mask, B, N, idx, offsets);
+  else rc_launch(compact_kernel<true>, dim3(1), dim3(1024), 0, s, mask, B, N, idx, offsets);
   return hipGetLastError();
 }
 

@@ -24,7 +24,8 @@ def _model(gh, gw):
 
 
 @pytest.mark.parametrize("gh,gw,batch,nd,radius", [(8, 8, 1, 1, 1), (8, 24, 1, 8, 2), (64, 33, 1, 3, 4), (33, 64, 3, 5, 0),
-                                                   (64, 64, 1, 6, 1), (65, 64, 1, 6, 1), (128, 128, 2, 7, 3)])
+                                                   (64, 64, 1, 6, 1), (65, 64, 1, 6, 1), (128, 128, 2, 7, 3),
+                                                   (8, 8, 300, 2, 1), (16, 12, 90, 4, 1), (64, 48, 7, 1, 2), (32, 32, 17, 8, 1)])
 def test_localize_edges(gh, gw, batch, nd, radius):
     print("localize", gh, gw, batch, nd, radius, flush=True)
     rng = np.random.default_rng(gh * gw + nd)
@@ -53,7 +54,9 @@ def test_localize_edges(gh, gw, batch, nd, radius):
     assert act.offsets.cpu().tolist() == list(act.host)
 
 
-@pytest.mark.parametrize("batch,tokens", [(1, 1), (2, 63), (3, 1025), (1, 16384), (2, 16385), (1, 65535)])
+@pytest.mark.parametrize("batch,tokens", [(1, 1), (2, 63), (3, 1025), (1, 16384), (2, 16385), (1, 65535),
+                                          (40, 1), (700, 3), (300, 64), (20, 1000), (257, 64), (64, 1024), (5, 16384),
+                                          (3, 65535)])
 def test_compact_edges(batch, tokens):
     print("compact", batch, tokens, flush=True)
     masks = (np.random.default_rng(tokens).random((batch, tokens)) < 0.4).astype(np.uint8) * 3
