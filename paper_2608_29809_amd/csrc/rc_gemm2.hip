@@ -793,10 +793,12 @@ GemmPlan plan_gemm_small(int M, int N, int K, size_t partial_cap_floats) {
 // us, fitted to launches of the step's shapes at 723 to 16384 rows (N 1152,
 // 3456, 4608; K 1152, 4608):
 // * this file's kernels: wide outputs 25 per round of 512 128x128 tiles (17
-//   where one round of 256 holds them); narrow ones 9 + 0.031 per 64x128 tile,
-//   at K = 4608 16 + 0.1 per tile and, split in two, 8 + 0.13 with the sum
-//   (11 more where two halves of 64x128 tiles of two K groups, one workgroup
-//   per CU, take a second round);
+//   where one round of 256 holds them); narrow ones 9 + 0.031 per 64x128 tile
+//   at K = 1152, less below it (at K = 128 and 1100 rows 8.0 where 128x144
+//   tiles take 11.0, at K = 512 and 1639 rows 10.5 and 14.4, at 4096 rows 18.0
+//   and 17.2); at K = 4608 16 + 0.1 per tile and, split in two, 8 + 0.13 with
+//   the sum (11 more where two halves of 64x128 tiles of two K groups, one
+//   workgroup per CU, take a second round);
 // * large tiles: per round, the stages' time and the ends (first stage,
 //   epilogue); a residual epilogue's ends are at least its traffic at 5.5 TB/s;
 //   with two workgroups per CU the ends overlap the other's stages but for 6;
@@ -811,9 +813,9 @@ GemmPlan plan_gemm(int M, int N, int K, size_t partial_cap_floats, int epi) {
   if (N % 144 || K % 64 || M < 256) return small;
   const bool down = K >= 2048 && epi == EPI_RESID;
   const double t64 = std::ceil(M / 64.0) * (N / 128.0), t128 = std::ceil(M / 128.0) * (N / 128.0);
-  const double mn = (double)M * N, norm = down ? 2.0 + mn * 6.0 / 4e6 : 0.0;
+  const double kk = std::min(1.0, K / 1152.0), mn = (double)M * N, norm = down ? 2.0 + mn * 6.0 / 4e6 : 0.0;
   double best = N >= 3072 ? (t128 <= 256 ? 17.0 : 25.0 * std::ceil(t128 / 512))
-                : K < 2048 ? 9.0 + 0.031 * t64
+                : K < 2048 ? 5.0 + 4.0 * kk + 0.031 * t64 * (0.3 + 0.7 * kk)
                 : small.splits > 1 ? 8.0 + 0.13 * t64 + (t64 > 128 && t64 < 160 ? 11.0 : 0.0) : 16.0 + 0.1 * t64 + norm;
   GemmPlan p = small;
   struct Tile { int bm, bn, kg, slots; double stage, ends[3]; };  // ends: stores, residual, GELU

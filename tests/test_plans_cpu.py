@@ -33,3 +33,14 @@ def test_plan_is_steady_in_the_row_count():
             if p != last:
                 assert last is None or M - start >= 32, (N, K, epi, start, M, last, p)
                 last, start = p, M
+
+
+def test_a_short_sum_keeps_the_small_tiles():
+    """Narrow outputs of up to 2458 rows take the small tiles at every depth of
+    the sum up to the model's width, where they measured faster; from a depth
+    of 512 on, 4096 rows take the large ones."""
+    for K in (64, 128, 256, 512, 768, 1024, 1152):
+        for M in (256, 723, 1100, 1639, 2458):
+            assert not gemm_plan(M, 1152, K, "resid")[0], (M, K)
+        if K >= 512:
+            assert gemm_plan(4096, 1152, K, "resid")[0], K
